@@ -26,6 +26,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <type_traits>
 #include <utility>
 
 #include "colsum.h"
@@ -62,158 +63,6 @@ struct GemmArgs {
   // which the split-K reduction adds in split order.
   uint16_t* db;
   float* dbp;
-};
-
-// Loader of one operand tile (ROWS output rows x BK reduction values) into
-// registers, then into LDS as [row][k].  KMAJ: element (r,k) at base[r*ld + k];
-// otherwise at base[k*ld + r].
-template <int ROWS, int BK, int NT, bool KMAJ, bool VEC>
-struct TileLoader {
-  // k rows per lane for an mn-major operand: 4 when the tile is large enough,
-  // else 2, so that every lane owns whole units
-  static constexpr int KR = (ROWS * BK / 8) / NT >= 4 ? 4 : 2;
-  static constexpr int UNITS = KMAJ ? ROWS * BK / 8 : ROWS * BK / (8 * KR);
-  static constexpr int PER = UNITS / NT;                         // units per lane
-  static_assert(UNITS % NT == 0, "tile does not split evenly over the workgroup");
-  uint4 reg[KMAJ ? PER : PER * KR];
-
-  // rows_valid: rows r < rows_valid exist; k_valid: reduction values k < k_valid exist.
-  //
-  // VEC (16-byte aligned base, leading dimension a multiple of 8): every load
-  // is a plain 16-byte load with no branch, so the compiler keeps the next
-  // stage's loads in flight.  A vector that starts inside the matrix lies
-  // wholly inside its row's leading dimension (ld is a multiple of 8 and at
-  // least the row length), so it is loaded whole and its elements past the
-  // end are zeroed; a vector that starts outside is redirected to the tile's
-  // first vector (always inside) and zeroed entirely.
-  __device__ __forceinline__ static uint4 mask_vec(uint4 v, int nvalid) {
-    // keep elements [0, nvalid) of 8, zero the rest
-    const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-    uint32_t o[4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const uint32_t lo = 2 * q < nvalid ? 0x0000FFFFu : 0u;
-      const uint32_t hi = 2 * q + 1 < nvalid ? 0xFFFF0000u : 0u;
-      o[q] = w[q] & (lo | hi);
-    }
-    return make_uint4(o[0], o[1], o[2], o[3]);
-  }
-
-  // extent of the tile last loaded (the masking happens in store(), next to
-  // the LDS writes, so that nothing waits on the loads before then)
-  int rv_ = ROWS, kv_ = BK;
-
-  __device__ __forceinline__ void load(const uint16_t* __restrict__ base, int64_t ld, int rows_valid,
-                                       int k_valid, int tid) {
-    rv_ = rows_valid;
-    kv_ = k_valid;
-    // a whole tile (the common case) needs no clamping or masking; the test
-    // is uniform over the workgroup, so it costs one scalar branch
-    const bool full = rows_valid >= ROWS && k_valid >= BK;
-    if constexpr (!VEC) {
-      load_guarded(base, ld, rows_valid, k_valid, tid);
-    } else {
-#pragma unroll
-      for (int u = 0; u < PER; ++u) {
-        const int unit = tid + u * NT;
-        if constexpr (KMAJ) {
-          const int r = unit / (BK / 8);
-          const int k = (unit % (BK / 8)) * 8;
-          const bool inside = full || (r < rows_valid && k < k_valid);
-          const int64_t off = inside ? (int64_t)r * ld + k : 0;
-          reg[u] = *reinterpret_cast<const uint4*>(base + off);
-        } else {
-          const int r = (unit / (BK / KR)) * 8;
-          const int k = (unit % (BK / KR)) * KR;
-#pragma unroll
-          for (int q = 0; q < KR; ++q) {
-            const bool inside = full || (k + q < k_valid && r < rows_valid);
-            const int64_t off = inside ? (int64_t)(k + q) * ld + r : 0;
-            reg[u * KR + q] = *reinterpret_cast<const uint4*>(base + off);
-          }
-        }
-      }
-    }
-  }
-
-  __device__ __forceinline__ void load_guarded(const uint16_t* __restrict__ base, int64_t ld,
-                                               int rows_valid, int k_valid, int tid) {
-    auto pack8 = [](const uint16_t (&h)[8]) {
-      return make_uint4(h[0] | ((uint32_t)h[1] << 16), h[2] | ((uint32_t)h[3] << 16),
-                        h[4] | ((uint32_t)h[5] << 16), h[6] | ((uint32_t)h[7] << 16));
-    };
-#pragma unroll
-    for (int u = 0; u < PER; ++u) {
-      const int unit = tid + u * NT;
-      if constexpr (KMAJ) {
-        const int r = unit / (BK / 8);
-        const int k = (unit % (BK / 8)) * 8;
-        const uint16_t* p = base + (int64_t)r * ld + k;
-        uint16_t h[8];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) h[j] = (r < rows_valid && k + j < k_valid) ? p[j] : (uint16_t)0;
-        reg[u] = pack8(h);
-      } else {
-        const int r = (unit / (BK / KR)) * 8;
-        const int k = (unit % (BK / KR)) * KR;
-#pragma unroll
-        for (int q = 0; q < KR; ++q) {
-          const uint16_t* p = base + (int64_t)(k + q) * ld + r;
-          uint16_t h[8];
-#pragma unroll
-          for (int j = 0; j < 8; ++j) h[j] = (k + q < k_valid && r + j < rows_valid) ? p[j] : (uint16_t)0;
-          reg[u * KR + q] = pack8(h);
-        }
-      }
-    }
-  }
-
-  // LDS tile: ROWS rows of pitch LDSP halves.
-  template <int LDSP>
-  __device__ __forceinline__ void store(uint16_t* __restrict__ lds, int tid) const {
-    const int rv_ = this->rv_, kv_ = this->kv_;
-    const bool full = rv_ >= ROWS && kv_ >= BK;
-#pragma unroll
-    for (int u = 0; u < PER; ++u) {
-      const int unit = tid + u * NT;
-      if constexpr (KMAJ) {
-        const int r = unit / (BK / 8);
-        const int k = (unit % (BK / 8)) * 8;
-        uint4 v = reg[u];
-        if (VEC && !full) v = mask_vec(v, r < rv_ && k < kv_ ? min(8, kv_ - k) : 0);
-        *reinterpret_cast<uint4*>(lds + r * LDSP + k) = v;
-      } else {
-        const int r = (unit / (BK / KR)) * 8;
-        const int k = (unit % (BK / KR)) * KR;
-        // register transpose: lane holds rows k..k+KR-1 of 8 consecutive
-        // output indices; write output index r+j as KR consecutive k values
-        uint32_t w[KR][4];
-#pragma unroll
-        for (int q = 0; q < KR; ++q) {
-          uint4 v = reg[u * KR + q];
-          if (VEC && !full) v = mask_vec(v, k + q < kv_ && r < rv_ ? min(8, rv_ - r) : 0);
-          w[q][0] = v.x;
-          w[q][1] = v.y;
-          w[q][2] = v.z;
-          w[q][3] = v.w;
-        }
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-          const int i = j >> 1;
-          uint32_t d[KR / 2];
-#pragma unroll
-          for (int q = 0; q < KR / 2; ++q) {
-            const uint32_t a = w[2 * q][i], b = w[2 * q + 1][i];
-            d[q] = (j & 1) ? ((a >> 16) | (b & 0xFFFF0000u)) : ((a & 0xFFFFu) | (b << 16));
-          }
-          if constexpr (KR == 4)
-            *reinterpret_cast<uint2*>(lds + (r + j) * LDSP + k) = make_uint2(d[0], d[1]);
-          else
-            *reinterpret_cast<uint32_t*>(lds + (r + j) * LDSP + k) = d[0];
-        }
-      }
-    }
-  }
 };
 
 // Output tile of this workgroup.  Workgroups are dealt to the 8 XCDs
@@ -254,22 +103,40 @@ __device__ __forceinline__ void tile_origin(int64_t M, int64_t N, int64_t& m0, i
 enum : int { EPI_BIAS = 1, EPI_GELU = 2, EPI_DACT = 4, EPI_RESID = 8, EPI_COUNT = 16,
              EPI_GENERIC = -1 };
 
-// Whole-tile epilogue through LDS, for the transposed accumulator layout and
-// 32 x 64 or 64 x 64 wave tiles.  Step 1 (accumulator layout: lane = one row, runs of 4
-// consecutive columns): h = half(acc + bias), written to the wave's own
-// [rows][68] half region of the LDS the main loop no longer needs.  Step 2 (row
-// layout: lane = 8 consecutive columns of one row): the pre-activation store,
-// GELU, GELU' of the previous layer and the residual add with 16-byte
-// accesses, each store writing 8 rows x 128 contiguous bytes.
+// 16 bytes at any 2-byte aligned address (one instruction: global accesses
+// need no alignment on gfx950)
+typedef u32x4 u32x4_any __attribute__((aligned(2)));
+
+// Epilogue through LDS, for the transposed accumulator layout.  Step 1
+// (accumulator layout: lane = one row, runs of 4 consecutive columns):
+// h = half(acc + bias), written to the wave's own [WM][WN + 4] half region of
+// the LDS the main loop no longer needs.  Step 2 (row layout: lane = 8
+// consecutive columns of one row): the pre-activation store, GELU, GELU' of
+// the previous layer and the residual add with 16-byte accesses, each store
+// of a 64-wide wave tile writing 8 rows x 128 contiguous bytes.
+// E: the epilogue operations, compiled in; EPI_GENERIC tests the call's
+// arguments instead.  EDGE = false: the wave's whole tile lies inside the
+// output and every operand is 16-byte aligned.  EDGE = true: rows from mv and
+// columns from nv on lie outside (either may be <= 0) and no alignment is
+// assumed; vectors inside the output keep the 16-byte accesses, only those
+// that straddle its last column go one value at a time.
 // pf (nullable): the wave's GELU' or residual operand rows, already loaded
 // in the row layout (16 bytes of row (lane >> 3) + 8 t per entry t).
-template <int DT, int TM, int TN, int E>
+template <int DT, int TM, int TN, int E, bool EDGE = false>
 __device__ __forceinline__ void gemm_epilogue_lds(const GemmArgs& g, const f32x16 (&acc)[TM][TN],
                                                   int64_t mw, int64_t nw, int lane, int64_t offC,
-                                                  uint16_t* lds, const u32x4* pf = nullptr) {
-  static_assert((TM == 1 || TM == 2) && TN == 2, "32 x 64 or 64 x 64 wave tiles");
-  constexpr int PITCH = 68;  // halves (34 banks): a column of 32 rows spreads over all banks
+                                                  uint16_t* lds, const u32x4* pf = nullptr, int mv = 0,
+                                                  int nv = 0) {
+  constexpr int WN = 32 * TN, PITCH = WN + 4;  // a column of 32 rows spreads over all banks
+  constexpr int LPR = WN / 8, RPT = 64 / LPR;  // lanes per row, rows per step
+  using vec = std::conditional_t<EDGE, u32x4_any, u32x4>;
   const int hi = lane >> 5, r32 = lane & 31;
+  const bool do_bias = E == EPI_GENERIC ? g.bias != nullptr : (E & EPI_BIAS) != 0;
+  const bool do_pre = E == EPI_GENERIC ? g.pre != nullptr : (E & EPI_GELU) != 0;
+  const bool do_gelu = E == EPI_GENERIC ? g.act == MPX_ACT_GELU_TANH : (E & EPI_GELU) != 0;
+  const bool do_dact = E == EPI_GENERIC ? g.dact != nullptr : (E & EPI_DACT) != 0;
+  const bool do_res = E == EPI_GENERIC ? g.resid != nullptr : (E & EPI_RESID) != 0;
+  const bool do_count = E == EPI_GENERIC ? g.nonfinite != nullptr : (E & EPI_COUNT) != 0;
   auto unpack = [](u32x2 w, float (&f)[4]) {
     f[0] = h2f<DT>((uint16_t)(w.x & 0xFFFFu));
     f[1] = h2f<DT>((uint16_t)(w.x >> 16));
@@ -281,7 +148,15 @@ __device__ __forceinline__ void gemm_epilogue_lds(const GemmArgs& g, const f32x1
     for (int q = 0; q < 4; ++q) {
       const int col = 32 * j + 8 * q + 4 * hi;
       float b[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-      if constexpr ((E & EPI_BIAS) != 0) unpack(ld_u2(g.bias + nw + col), b);
+      if (do_bias) {
+        if constexpr (EDGE) {
+#pragma unroll
+          for (int c = 0; c < 4; ++c)
+            if (col + c < nv) b[c] = h2f<DT>(g.bias[nw + col + c]);
+        } else {
+          unpack(ld_u2(g.bias + nw + col), b);
+        }
+      }
       static_for<TM>([&](auto i) {
         const int row = 32 * i + r32;
         uint16_t h[4];
@@ -292,12 +167,12 @@ __device__ __forceinline__ void gemm_epilogue_lds(const GemmArgs& g, const f32x1
       });
     }
   });
-  const int c8 = 8 * (lane & 7);
+  const int c8 = 8 * (lane % LPR);
   const int64_t ldc = g.ldc;
   uint16_t* C = g.C + (offC + mw * ldc + nw);
-  uint16_t* pre = (E & EPI_GELU) ? g.pre + (mw * ldc + nw) : nullptr;
-  const uint16_t* dact = (E & EPI_DACT) ? g.dact + (mw * ldc + nw) : nullptr;
-  const uint16_t* res = (E & EPI_RESID) ? g.resid + (mw * g.ldr + nw) : nullptr;
+  uint16_t* pre = do_pre ? g.pre + (mw * ldc + nw) : nullptr;
+  const uint16_t* dact = do_dact ? g.dact + (mw * ldc + nw) : nullptr;
+  const uint16_t* res = do_res ? g.resid + (mw * g.ldr + nw) : nullptr;
   auto h8 = [](u32x4 w, uint16_t (&h)[8]) {
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
@@ -309,39 +184,70 @@ __device__ __forceinline__ void gemm_epilogue_lds(const GemmArgs& g, const f32x1
     return u32x4{h[0] | ((uint32_t)h[1] << 16), h[2] | ((uint32_t)h[3] << 16),
                  h[4] | ((uint32_t)h[5] << 16), h[6] | ((uint32_t)h[7] << 16)};
   };
+  using off_t = std::conditional_t<EDGE, int64_t, uint32_t>;
+  // one row's 8 columns; nc of them exist (8 unless EDGE)
+  const int nc = EDGE ? min(8, nv - c8) : 8;
+  auto load8 = [&](const uint16_t* p, uint16_t (&h)[8]) {
+    if (!EDGE || nc == 8) {
+      h8(*reinterpret_cast<const vec*>(p), h);
+    } else {
+#pragma unroll
+      for (int c = 0; c < 8; ++c) h[c] = c < nc ? p[c] : (uint16_t)0;
+    }
+  };
+  auto store8 = [&](uint16_t* p, const uint16_t (&h)[8]) {
+    if (!EDGE || nc == 8) {
+      *reinterpret_cast<vec*>(p) = p8(h);
+    } else {
+#pragma unroll
+      for (int c = 0; c < 8; ++c)
+        if (c < nc) p[c] = h[c];
+    }
+  };
   int bad = 0;
 #pragma unroll
-  for (int t = 0; t < 4 * TM; ++t) {
-    const int row = (lane >> 3) + 8 * t;
+  for (int t = 0; t < 32 * TM / RPT; ++t) {
+    const int row = lane / LPR + RPT * t;
     const u32x2 w0 = *reinterpret_cast<const u32x2*>(lds + row * PITCH + c8);
     const u32x2 w1 = *reinterpret_cast<const u32x2*>(lds + row * PITCH + c8 + 4);
+    if constexpr (EDGE) {
+      if (row >= mv || nc <= 0) continue;
+    }
     uint16_t h[8];
     h8(u32x4{w0.x, w0.y, w1.x, w1.y}, h);
-    const uint32_t off = (uint32_t)(row * ldc + c8);
-    if constexpr ((E & EPI_GELU) != 0) {
-      *reinterpret_cast<u32x4*>(pre + off) = p8(h);
+    const off_t off = (off_t)(row * ldc + c8);
+    if (do_pre) store8(pre + off, h);
+    if (do_gelu) {
 #pragma unroll
       for (int c = 0; c < 8; ++c) h[c] = f2h<DT>(gelu_tanh(h2f<DT>(h[c])));
     }
-    if constexpr ((E & EPI_DACT) != 0) {
+    if (do_dact) {
       uint16_t da[8];
-      h8(pf ? pf[t] : *reinterpret_cast<const u32x4*>(dact + off), da);
+      if (!EDGE && pf) h8(pf[t], da);
+      else load8(dact + off, da);
 #pragma unroll
       for (int c = 0; c < 8; ++c) h[c] = f2h<DT>(h2f<DT>(h[c]) * gelu_tanh_grad(h2f<DT>(da[c])));
     }
-    if constexpr ((E & EPI_RESID) != 0) {
+    if (do_res) {
       uint16_t rv[8];
-      h8(pf ? pf[t] : *reinterpret_cast<const u32x4*>(res + (uint32_t)(row * g.ldr + c8)), rv);
+      if (!EDGE && pf) h8(pf[t], rv);
+      else load8(res + (off_t)(row * g.ldr + c8), rv);
 #pragma unroll
       for (int c = 0; c < 8; ++c) h[c] = f2h<DT>(h2f<DT>(h[c]) + h2f<DT>(rv[c]));
     }
-    const u32x4 o = p8(h);
-    if constexpr ((E & EPI_COUNT) != 0)  // no branch inside the store loop
-      bad += nonfinite2<DT>(o[0]) + nonfinite2<DT>(o[1]) + nonfinite2<DT>(o[2]) +
-             nonfinite2<DT>(o[3]);
-    *reinterpret_cast<u32x4*>(C + off) = o;
+    if (do_count) {
+      if (!EDGE || nc == 8) {  // no branch inside the store loop
+        const u32x4 o = p8(h);
+        bad += nonfinite2<DT>(o[0]) + nonfinite2<DT>(o[1]) + nonfinite2<DT>(o[2]) +
+               nonfinite2<DT>(o[3]);
+      } else {
+#pragma unroll
+        for (int c = 0; c < 8; ++c) bad += (c < nc && h_nonfinite<DT>(h[c])) ? 1 : 0;
+      }
+    }
+    store8(C + off, h);
   }
-  if constexpr ((E & EPI_COUNT) != 0) add_nonfinite(g.nonfinite, bad);
+  if (do_count) add_nonfinite(g.nonfinite, bad);
 }
 
 // Generic epilogue shared by the GEMM kernels: any tile, any operand
@@ -455,111 +361,6 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs& g, const f32x16 (&
   if (g.nonfinite) add_nonfinite(g.nonfinite, bad);
 }
 
-// OCC: waves per SIMD the register budget is sized for.
-template <int DT, int BM, int BN, int BK, int WM, int WN, bool AK, bool BKM, bool VEC, int OCC>
-__global__ __launch_bounds__((BM / WM) * (BN / WN) * 64)
-__attribute__((amdgpu_waves_per_eu(OCC, OCC)))
-void gemm_kernel(GemmArgs g) {
-  constexpr int NW = (BM / WM) * (BN / WN);
-  constexpr int NT = NW * 64;
-  constexpr int PAD = 8;
-  constexpr int LDSP = BK + PAD;
-  constexpr int TM = WM / 32, TN = WN / 32;
-  // one LDS block: the double-buffered A and B tiles during the main loop,
-  // then the float32 staging area of the epilogue
-  __shared__ __attribute__((aligned(16))) uint16_t smem[2 * (BM + BN) * LDSP];
-  uint16_t (*sA)[BM * LDSP] = reinterpret_cast<uint16_t (*)[BM * LDSP]>(smem);
-  uint16_t (*sB)[BN * LDSP] = reinterpret_cast<uint16_t (*)[BN * LDSP]>(smem + 2 * BM * LDSP);
-
-  const int tid = threadIdx.x;
-  const int lane = tid & 63;
-  const int wave = tid >> 6;
-  const int wm0 = (wave / (BN / WN)) * WM;
-  const int wn0 = (wave % (BN / WN)) * WN;
-
-  int64_t m0, n0;
-  tile_origin<BM, BN>(g.M, g.N, m0, n0);
-  // batch / split
-  int64_t z = blockIdx.y;
-  int split = 0;
-  int64_t offA = 0, offB = 0, offC = 0;
-  if (g.splits > 1) {
-    split = (int)z;
-  } else {
-    const int64_t i0 = (uint32_t)z / (uint32_t)g.nb1, i1 = (uint32_t)z % (uint32_t)g.nb1;
-    offA = i0 * g.sA0 + i1 * g.sA1;
-    offB = i0 * g.sB0 + i1 * g.sB1;
-    offC = i0 * g.sC0 + i1 * g.sC1;
-  }
-  const int64_t kbeg = (int64_t)split * g.k_split;
-  const int64_t kend = min(g.K, kbeg + g.k_split);
-  const int nk = (int)((kend - kbeg + BK - 1) / BK);
-
-  const uint16_t* A = g.A + offA;
-  const uint16_t* B = g.B + offB;
-  // operand tile base pointers at k = kbeg
-  const uint16_t* Ab = AK ? A + m0 * g.lda + kbeg : A + kbeg * g.lda + m0;
-  const uint16_t* Bb = BKM ? B + n0 * g.ldb + kbeg : B + kbeg * g.ldb + n0;
-  const int64_t Astep = AK ? BK : BK * g.lda;
-  const int64_t Bstep = BKM ? BK : BK * g.ldb;
-  const int rowsA = (int)min<int64_t>(BM, g.M - m0);
-  const int rowsB = (int)min<int64_t>(BN, g.N - n0);
-
-  // One register stage: the loads of k tile kt+1 are issued before the MFMAs
-  // of tile kt and land in LDS (the other buffer) after them.
-  TileLoader<BM, BK, NT, AK, VEC> la;
-  TileLoader<BN, BK, NT, BKM, VEC> lb;
-
-  f32x16 acc[TM][TN];
-  static_for<TM>([&](auto i) {
-    static_for<TN>([&](auto j) {
-#pragma unroll
-      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.0f;
-    });
-  });
-
-  auto kvalid = [&](int kt) { return (int)min<int64_t>(BK, kend - (kbeg + (int64_t)kt * BK)); };
-  if (nk > 0) {
-    la.load(Ab, g.lda, rowsA, kvalid(0), tid);
-    lb.load(Bb, g.ldb, rowsB, kvalid(0), tid);
-    la.template store<LDSP>(sA[0], tid);
-    lb.template store<LDSP>(sB[0], tid);
-  }
-  __syncthreads();
-
-  for (int kt = 0; kt < nk; ++kt) {
-    const int c = kt & 1;
-    const bool more = kt + 1 < nk;
-    if (more) {
-      la.load(Ab + (kt + 1) * Astep, g.lda, rowsA, kvalid(kt + 1), tid);
-      lb.load(Bb + (kt + 1) * Bstep, g.ldb, rowsB, kvalid(kt + 1), tid);
-    }
-    const uint16_t* a_s = sA[c];
-    const uint16_t* b_s = sB[c];
-#pragma unroll
-    for (int kk = 0; kk < BK / 16; ++kk) {
-      const int kofs = kk * 16 + 8 * (lane >> 5);
-      uint4 af[TM], bf[TN];
-#pragma unroll
-      for (int i = 0; i < TM; ++i)
-        af[i] = *reinterpret_cast<const uint4*>(a_s + (wm0 + i * 32 + (lane & 31)) * LDSP + kofs);
-#pragma unroll
-      for (int j = 0; j < TN; ++j)
-        bf[j] = *reinterpret_cast<const uint4*>(b_s + (wn0 + j * 32 + (lane & 31)) * LDSP + kofs);
-      static_for<TM>([&](auto i) {
-        static_for<TN>([&](auto j) { acc[i][j] = mfma32<DT>(af[i], bf[j], acc[i][j]); });
-      });
-    }
-    if (more) {
-      la.template store<LDSP>(sA[c ^ 1], tid);
-      lb.template store<LDSP>(sB[c ^ 1], tid);
-    }
-    __syncthreads();
-  }
-
-  gemm_epilogue<DT, TM, TN>(g, acc, m0 + wm0, n0 + wn0, lane, split, offC);
-}
-
 // ------------------------------------------------- direct-to-LDS kernel --
 //
 // The main loop of the kernel below moves operand tiles from global memory
@@ -601,6 +402,17 @@ __device__ __forceinline__ void wait_vmcnt() {
   asm volatile("s_waitcnt vmcnt(%0)" : : "n"(N) : "memory");
 }
 
+// Position of 16-byte chunk c of row r (k-major: output row of 64 k; mn-major:
+// k row of ROWS outputs) within the row in LDS; its own inverse.  An mn-major
+// row of 64 outputs spans half the banks, so there rows 2 and 3 of each four
+// move to the other half of their row.
+template <int ROWS, bool KMAJ>
+__device__ __forceinline__ int dma_chunk(int r, int c) {
+  if constexpr (KMAJ) return c ^ ((r >> 1) & 7);
+  else if constexpr (ROWS == 64) return c ^ (4 * ((r >> 1) & 1));
+  else return c ^ (4 * (r & 3));
+}
+
 // One operand of the direct-to-LDS kernel: ROWS output rows (of M or N) by
 // 64 k per stage, copied by NWAVES waves, Q copies per wave.
 template <int ROWS, bool KMAJ, int NWAVES>
@@ -608,7 +420,7 @@ struct DmaOperand {
   static constexpr int BLOCKS = ROWS / 8;  // 1 KiB copies per stage
   static constexpr int Q = BLOCKS / NWAVES;
   static_assert(BLOCKS % NWAVES == 0, "copies do not split evenly over the waves");
-  static_assert(KMAJ || ROWS == 128 || ROWS == 256, "mn-major tiles are 128 or 256 wide");
+  static_assert(KMAJ || ROWS == 64 || ROWS == 128 || ROWS == 256, "mn-major tile widths");
   uint32_t off[Q];  // per-lane byte offsets of the copies, relative to the tile base
   int64_t step;     // bytes from one k tile to the next
 
@@ -619,7 +431,7 @@ struct DmaOperand {
 #pragma unroll
       for (int q = 0; q < Q; ++q) {
         const int r = 8 * (wave + NWAVES * q) + (lane >> 3);
-        const int c = (lane & 7) ^ ((r >> 1) & 7);
+        const int c = dma_chunk<ROWS, true>(r, lane & 7);
         off[q] = (uint32_t)(min(r, rv - 1) * ld * 2 + c * 16);
       }
     } else {
@@ -629,7 +441,7 @@ struct DmaOperand {
 #pragma unroll
       for (int q = 0; q < Q; ++q) {
         const int kr = RPB * (wave + NWAVES * q) + lane / CH;
-        const int c = (lane % CH) ^ (4 * (kr & 3));
+        const int c = dma_chunk<ROWS, false>(kr, lane % CH);
         off[q] = (uint32_t)(kr * ld * 2 + (8 * c < rv ? 16 * c : 0));
       }
     }
@@ -645,6 +457,81 @@ struct DmaOperand {
 #pragma unroll
     for (int q = 0; q < Q; ++q)
       dma16(sbase, off[q], slds + 1024u * (uint32_t)(wave + NWAVES * q));
+  }
+};
+
+// The same operand staged through registers, for operands the copies cannot
+// take (rows that are not 16-byte aligned, a reduction that is not a multiple
+// of 64): 16-byte loads at any alignment, written to the LDS positions the
+// copies would have filled, so the fragment reads are the same.  Vectors that
+// would reach past the end of their row (the last k of a k-major row, the
+// last output of an mn-major one) are loaded ending at the row's last element
+// and shifted down, with zeros behind: no access leaves the matrix.
+// Extents below 8 (no whole vector in a row) load one value at a time.
+template <int ROWS, bool KMAJ, int NWAVES>
+struct StagedOperand {
+  static constexpr int BLOCKS = ROWS / 8, Q = BLOCKS / NWAVES;
+  static_assert(BLOCKS % NWAVES == 0, "blocks do not split evenly over the waves");
+  static constexpr int CH = KMAJ ? 8 : ROWS / 8;
+  u32x4 v[Q];
+  const uint16_t* base;  // tile's first element at the split's first k
+  int64_t ld;
+  int c8;    // first k (k-major) or output (mn-major) of the lane's vectors within the tile
+  int r0;    // output row (k-major) or k row (mn-major) of the lane's vector 0
+  int rv;    // rows of the matrix from the tile's first on
+  int krem;  // reduction values from the loaded tile's first on
+  bool tiny;
+
+  // extent: length of a row of the operand's storage (K or the output count)
+  __device__ __forceinline__ void init(const uint16_t* base_, int64_t ld_, int64_t rows_left, int64_t extent,
+                                       int wave, int lane) {
+    base = base_;
+    ld = ld_;
+    rv = (int)min<int64_t>(rows_left, 1 << 20);
+    tiny = extent < 8;
+    const int blk = 64 / CH;  // rows per 1 KiB block
+    r0 = blk * wave + lane / CH;
+    c8 = 8 * dma_chunk<ROWS, KMAJ>(r0, lane % CH);
+  }
+  __device__ __forceinline__ void load(int64_t k0, int krem_) {
+    krem = krem_;
+    const int n = KMAJ ? krem : rv;  // elements from the tile's first on in the vector's direction
+    const int start = min(c8, n - 8);
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      const int r = min(r0 + 64 / CH * NWAVES * q, (KMAJ ? rv : krem) - 1);
+      const uint16_t* row = KMAJ ? base + (int64_t)r * ld + k0 : base + (k0 + r) * ld;
+      if (!tiny) {
+        v[q] = *reinterpret_cast<const u32x4_any*>(row + start);
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const uint32_t lo = c8 + 2 * e < n ? row[c8 + 2 * e] : (uint16_t)0;
+          const uint32_t hi = c8 + 2 * e + 1 < n ? row[c8 + 2 * e + 1] : (uint16_t)0;
+          v[q][e] = lo | (hi << 16);
+        }
+      }
+    }
+  }
+  __device__ __forceinline__ void store(uint8_t* lds, int wave, int lane) {
+    const bool whole = (KMAJ ? krem : rv) >= (KMAJ ? 64 : ROWS) || tiny;
+    const int sh = c8 - min(c8, (KMAJ ? krem : rv) - 8);
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      u32x4 x = v[q];
+      if (!whole) x = shr_halves(x, sh);
+      if (!KMAJ && r0 + 64 / CH * NWAVES * q >= krem) x = u32x4{0u, 0u, 0u, 0u};
+      *reinterpret_cast<u32x4*>(lds + 1024 * (wave + NWAVES * q) + 16 * lane) = x;
+    }
+  }
+  // x with its first s elements dropped and zeros after the rest
+  __device__ __forceinline__ static u32x4 shr_halves(u32x4 x, int s) {
+    const u32x4 o = {__builtin_amdgcn_alignbit(x[1], x[0], 16), __builtin_amdgcn_alignbit(x[2], x[1], 16),
+                     __builtin_amdgcn_alignbit(x[3], x[2], 16), x[3] >> 16};
+    x = (s & 1) ? o : x;
+    x = (s & 2) ? u32x4{x[1], x[2], x[3], 0u} : x;
+    x = (s & 4) ? u32x4{x[2], x[3], 0u, 0u} : x;
+    return s >= 8 ? u32x4{0u, 0u, 0u, 0u} : x;
   }
 };
 
@@ -665,7 +552,7 @@ struct FragReader {
 #pragma unroll
       for (int i = 0; i < T; ++i) {
         const int m = w0 + 32 * i + 16 * (g & 1) + 4 * t;
-        base[i] = (uint32_t)(kr * ROWS * 2 + (((m >> 3) ^ (4 * e)) << 4) + (m & 7) * 2);
+        base[i] = (uint32_t)(kr * ROWS * 2 + (dma_chunk<ROWS, false>(e, m >> 3) << 4) + (m & 7) * 2);
       }
     }
   }
@@ -705,8 +592,16 @@ __device__ __forceinline__ float frag_sum8(const uint4& f) {
 // partial dbp[row][split * C + c] (the reduction adds a row's C x splits
 // partials with one wave, in a fixed order); without split-K column 0 sums
 // every k tile and writes db itself.
+//
+// STG: the operands go through registers (StagedOperand) instead of the
+// direct copies, with two stages; any alignment and any reduction length.
+// The loads of k tile kt + 2 are issued, and tile kt + 1 is written to the
+// other stage, ahead of the MFMAs of tile kt, so a load has a whole k step to
+// land.  Every tile takes the epilogue through LDS, which handles ragged
+// edges and unaligned rows there.  (One-value loads served these operands
+// before: 8415 x 768 x 588 in bf16 forward / dX / dW took 89 / 145 / 157 us.)
 template <int DT, int BM, int BN, int WM, int WN, int S, int OCC, bool AK, bool BKM, int E,
-          bool DBS = false>
+          bool DBS = false, bool STG = false>
 __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64)
 __attribute__((amdgpu_waves_per_eu(OCC, OCC)))
 void gemm_dma_kernel(GemmArgs g) {
@@ -716,6 +611,7 @@ void gemm_dma_kernel(GemmArgs g) {
   constexpr int STAGE = A_BYTES + B_BYTES;
   constexpr int L = (BM + BN) / 8 / NWAVES;  // copies per lane per stage
   static_assert((S - 2) * L <= 63, "vmcnt range");
+  static_assert(!STG || S == 2, "two stages");
   // LDS read instructions per k step (a k-major fragment is one 16-byte
   // read, an mn-major one two transposing 8-byte reads), per MFMA
   constexpr int kReads = TM * (AK ? 1 : 2) + TN * (BKM ? 1 : 2);
@@ -744,14 +640,19 @@ void gemm_dma_kernel(GemmArgs g) {
   }
   const int64_t kbeg = (int64_t)split * g.k_split;
   const int64_t kend = min(g.K, kbeg + g.k_split);
-  const int nk = (int)((kend - kbeg) / 64);
+  const int nk = (int)((kend - kbeg + (STG ? 63 : 0)) / 64);
 
   const uint16_t* Ab = g.A + offA + (AK ? m0 * g.lda + kbeg : kbeg * g.lda + m0);
   const uint16_t* Bb = g.B + offB + (BKM ? n0 * g.ldb + kbeg : kbeg * g.ldb + n0);
-  DmaOperand<BM, AK, NWAVES> da;
-  DmaOperand<BN, BKM, NWAVES> db;
-  da.init(g.lda, (int)min<int64_t>(BM, g.M - m0), wave, lane);
-  db.init(g.ldb, (int)min<int64_t>(BN, g.N - n0), wave, lane);
+  std::conditional_t<STG, StagedOperand<BM, AK, NWAVES>, DmaOperand<BM, AK, NWAVES>> da;
+  std::conditional_t<STG, StagedOperand<BN, BKM, NWAVES>, DmaOperand<BN, BKM, NWAVES>> db;
+  if constexpr (STG) {
+    da.init(Ab, g.lda, g.M - m0, AK ? g.K : g.M, wave, lane);
+    db.init(Bb, g.ldb, g.N - n0, BKM ? g.K : g.N, wave, lane);
+  } else {
+    da.init(g.lda, (int)min<int64_t>(BM, g.M - m0), wave, lane);
+    db.init(g.ldb, (int)min<int64_t>(BN, g.N - n0), wave, lane);
+  }
   FragReader<BM, AK, TM> fa;
   FragReader<BN, BKM, TN> fb;
   fa.init(wm0, lane);
@@ -777,8 +678,8 @@ void gemm_dma_kernel(GemmArgs g) {
   // A whole tile's GELU' or residual operand is loaded into registers before
   // the first copies (the oldest loads, so the first tile's wait covers
   // them): the epilogue then starts without a memory round trip.
-  constexpr bool kPF = E != EPI_GENERIC && (E & (EPI_DACT | EPI_RESID)) != 0;
-  const bool whole = E != EPI_GENERIC && g.full_epi && m0 + BM <= g.M && n0 + BN <= g.N;
+  constexpr bool kPF = !STG && E != EPI_GENERIC && (E & (EPI_DACT | EPI_RESID)) != 0;
+  const bool whole = (STG || E != EPI_GENERIC) && g.full_epi && m0 + BM <= g.M && n0 + BN <= g.N;
   u32x4 pf[kPF ? 4 * TM : 1];
   if constexpr (kPF) {
     if (whole) {
@@ -791,25 +692,49 @@ void gemm_dma_kernel(GemmArgs g) {
   }
 
   auto issue = [&](int kt) {
-    const uint32_t st = lds0 + (uint32_t)((kt % S) * STAGE);
-    da.issue(reinterpret_cast<const uint16_t*>(reinterpret_cast<const uint8_t*>(Ab) + kt * da.step), st, wave);
-    db.issue(reinterpret_cast<const uint16_t*>(reinterpret_cast<const uint8_t*>(Bb) + kt * db.step),
-             st + A_BYTES, wave);
+    if constexpr (STG) {
+      const int krem = (int)min<int64_t>(kend - kbeg - 64 * (int64_t)kt, 1 << 20);
+      da.load(64 * (int64_t)kt, krem);
+      db.load(64 * (int64_t)kt, krem);
+    } else {
+      const uint32_t st = lds0 + (uint32_t)((kt % S) * STAGE);
+      da.issue(reinterpret_cast<const uint16_t*>(reinterpret_cast<const uint8_t*>(Ab) + kt * da.step), st, wave);
+      db.issue(reinterpret_cast<const uint16_t*>(reinterpret_cast<const uint8_t*>(Bb) + kt * db.step),
+               st + A_BYTES, wave);
+    }
   };
+  auto put = [&](int kt) {  // STG: the loaded k tile kt into its stage
+    if constexpr (STG) {
+      da.store(smem + (kt % S) * STAGE, wave, lane);
+      db.store(smem + (kt % S) * STAGE + A_BYTES, wave, lane);
+    }
+  };
+  if constexpr (STG) {
+    issue(0);
+    put(0);
+    if (nk > 1) issue(1);
+  } else {
 #pragma unroll
-  for (int s = 0; s < S - 1; ++s)
-    if (s < nk) issue(s);
+    for (int s = 0; s < S - 1; ++s)
+      if (s < nk) issue(s);
+  }
 
   for (int kt = 0; kt < nk; ++kt) {
     const bool db_now = dbw && kt == db_next;
     if (db_now) db_next += db_cols;
-    // tile kt has landed once at most min(S - 2, nk - 1 - kt) later tiles are in flight
-    const int later = min(S - 2, nk - 1 - kt);
-    static_for<S - 1>([&](auto p) {
-      if (later == p) wait_vmcnt<p * L>();
-    });
-    __syncthreads();
-    if (kt + S - 1 < nk) issue(kt + S - 1);
+    if constexpr (STG) {
+      __syncthreads();  // tile kt is in its stage, the other stage has been read
+      if (kt + 1 < nk) put(kt + 1);
+      if (kt + 2 < nk) issue(kt + 2);
+    } else {
+      // tile kt has landed once at most min(S - 2, nk - 1 - kt) later tiles are in flight
+      const int later = min(S - 2, nk - 1 - kt);
+      static_for<S - 1>([&](auto p) {
+        if (later == p) wait_vmcnt<p * L>();
+      });
+      __syncthreads();
+      if (kt + S - 1 < nk) issue(kt + S - 1);
+    }
     const uint32_t sa = lds0 + (uint32_t)((kt % S) * STAGE), sb = sa + A_BYTES;
     // fragments double-buffered over the four k steps of 16: the LDS reads
     // of step kk + 1 are issued ahead of the MFMAs of step kk.  Products
@@ -867,7 +792,19 @@ void gemm_dma_kernel(GemmArgs g) {
     }
   }
   // the accumulators hold C^T blocks (the MFMA operands are swapped above)
-  if constexpr (E != EPI_GENERIC) {
+  if constexpr (STG) {
+    if (g.splits == 1) {
+      __syncthreads();  // every wave is done reading the stage buffers
+      uint16_t* lds = reinterpret_cast<uint16_t*>(smem) + wave * (WM * (WN + 4));
+      if (whole)
+        gemm_epilogue_lds<DT, TM, TN, E>(g, acc, m0 + wm0, n0 + wn0, lane, offC, lds);
+      else
+        gemm_epilogue_lds<DT, TM, TN, E, true>(g, acc, m0 + wm0, n0 + wn0, lane, offC, lds, nullptr,
+                                               (int)min<int64_t>(WM, g.M - m0 - wm0),
+                                               (int)min<int64_t>(WN, g.N - n0 - wn0));
+      return;
+    }
+  } else if constexpr (E != EPI_GENERIC) {
     if (whole) {  // uniform over the workgroup
       __syncthreads();  // every wave is done reading the stage buffers
       gemm_epilogue_lds<DT, TM, TN, E>(g, acc, m0 + wm0, n0 + wn0, lane, offC,
@@ -1057,37 +994,8 @@ inline bool splitk_reduce_vec(const float* ws, int64_t MN, const uint16_t* C) {
 
 // ------------------------------------------------------------ dispatch --
 
-struct Cfg {
-  int bm, bn;
-};
-
 static bool aligned_vec(const void* p, int64_t ld, int64_t s0, int64_t s1) {
   return (reinterpret_cast<uintptr_t>(p) & 15u) == 0 && ld % 8 == 0 && s0 % 8 == 0 && s1 % 8 == 0;
-}
-
-template <int DT, int BM, int BN, int WM, int WN, int BK = 64, int OCC = 2>
-static hipError_t launch_cfg(const GemmArgs& g, bool ak, bool bk, bool vec, int64_t nbatch,
-                             hipStream_t s) {
-  constexpr int NT = (BM / WM) * (BN / WN) * 64;
-  const int64_t tiles = ((g.M + BM - 1) / BM) * ((g.N + BN - 1) / BN);
-  dim3 grid((unsigned)tiles, (unsigned)(g.splits > 1 ? g.splits : nbatch));
-#define MPX_G(AKv, BKv, VECv) \
-  gemm_kernel<DT, BM, BN, BK, WM, WN, AKv, BKv, VECv, OCC><<<grid, NT, 0, s>>>(g)
-  if (vec) {
-    if (ak && bk) MPX_G(true, true, true);
-    else if (ak && !bk) MPX_G(true, false, true);
-    else if (!ak && bk) MPX_G(false, true, true);
-    else MPX_G(false, false, true);
-  } else if constexpr (BM * BN <= 128 * 128) {  // unaligned operands: small tiles only
-    if (ak && bk) MPX_G(true, true, false);
-    else if (ak && !bk) MPX_G(true, false, false);
-    else if (!ak && bk) MPX_G(false, true, false);
-    else MPX_G(false, false, false);
-  } else {
-    return hipErrorInvalidValue;
-  }
-#undef MPX_G
-  return hipGetLastError();
 }
 
 // Epilogue mask of a call, or EPI_GENERIC when it has no compiled variant
@@ -1112,7 +1020,7 @@ static bool full_epilogue_ok(const GemmArgs& g, int bm) {
 }
 
 template <int DT, int BM, int BN, int WM, int WN, int S, int OCC>
-static hipError_t launch_dma(GemmArgs g, bool ak, bool bk, int64_t nbatch, hipStream_t s) {
+hipError_t launch_dma(GemmArgs g, bool ak, bool bk, int64_t nbatch, hipStream_t s) {
   constexpr int NT = (BM / WM) * (BN / WN) * 64;
   const int64_t tiles = ((g.M + BM - 1) / BM) * ((g.N + BN - 1) / BN);
   dim3 grid((unsigned)tiles, (unsigned)(g.splits > 1 ? g.splits : nbatch));
@@ -1182,8 +1090,46 @@ static hipError_t launch_dma(GemmArgs g, bool ak, bool bk, int64_t nbatch, hipSt
   return hipGetLastError();
 }
 
+// Operands staged through registers: any alignment, any reduction length.
+template <int DT, int BM, int BN, int WM, int WN>
+hipError_t launch_staged(GemmArgs g, bool ak, bool bk, int64_t nbatch, hipStream_t s) {
+  constexpr int NT = (BM / WM) * (BN / WN) * 64;
+  const int64_t tiles = ((g.M + BM - 1) / BM) * ((g.N + BN - 1) / BN);
+  dim3 grid((unsigned)tiles, (unsigned)(g.splits > 1 ? g.splits : nbatch));
+  g.full_epi = full_epilogue_ok(g, BM) ? 1 : 0;
+#define MPX_S(AKv, BKv, Ev, DBv) \
+  gemm_dma_kernel<DT, BM, BN, WM, WN, 2, 2, AKv, BKv, Ev, DBv, true><<<grid, NT, 0, s>>>(g)
+  if constexpr (BM == 128) {  // the training step's epilogues compiled in
+    const int e = epilogue_mask(g) | (g.nonfinite ? EPI_COUNT : 0);
+    if (ak && bk) {
+      switch (e) {
+        case EPI_BIAS: MPX_S(true, true, EPI_BIAS, false); break;
+        case EPI_BIAS | EPI_GELU: MPX_S(true, true, EPI_BIAS | EPI_GELU, false); break;
+        default: MPX_S(true, true, EPI_GENERIC, false);
+      }
+    } else if (ak) {
+      if (e == 0) MPX_S(true, false, 0, false);
+      else MPX_S(true, false, EPI_GENERIC, false);
+    } else if (bk) {
+      MPX_S(false, true, EPI_GENERIC, false);
+    } else if (g.db) {
+      MPX_S(false, false, EPI_GENERIC, true);
+    } else {
+      MPX_S(false, false, EPI_GENERIC, false);
+    }
+  } else {
+    if (ak && bk) MPX_S(true, true, EPI_GENERIC, false);
+    else if (ak) MPX_S(true, false, EPI_GENERIC, false);
+    else if (bk) MPX_S(false, true, EPI_GENERIC, false);
+    else if (g.db) MPX_S(false, false, EPI_GENERIC, true);
+    else MPX_S(false, false, EPI_GENERIC, false);
+  }
+#undef MPX_S
+  return hipGetLastError();
+}
+
 template <int DT, int BM, int BN, int WM, int WN, int OCC>
-static hipError_t launch_persistent(GemmArgs g, bool ak, bool bk, hipStream_t s) {
+hipError_t launch_persistent(GemmArgs g, bool ak, bool bk, hipStream_t s) {
   constexpr int NT = (BM / WM) * (BN / WN) * 64;
   const int64_t tiles = ((g.M + BM - 1) / BM) * ((g.N + BN - 1) / BN);
   const unsigned grid = (unsigned)std::min<int64_t>(tiles, 256 * OCC);
@@ -1211,9 +1157,32 @@ static hipError_t launch_persistent(GemmArgs g, bool ak, bool bk, hipStream_t s)
   return hipGetLastError();
 }
 
+// The launchers are compiled in three sources per half type, which build in
+// parallel: the configurations the dispatcher picks (gemm_f16.hip), the
+// register-staged ones (gemm_staged_f16.hip) and the ones only forced
+// (gemm_forced_f16.hip); likewise for bf16.
+#define MPX_GEMM_STAGED(X, DT)                                                              \
+  X template hipError_t launch_staged<DT, 64, 64, 32, 32>(GemmArgs, bool, bool, int64_t, hipStream_t); \
+  X template hipError_t launch_staged<DT, 128, 128, 64, 64>(GemmArgs, bool, bool, int64_t, hipStream_t);
+#define MPX_GEMM_FORCED(X, DT)                                                              \
+  X template hipError_t launch_dma<DT, 256, 256, 128, 128, 2, 1>(GemmArgs, bool, bool, int64_t, hipStream_t); \
+  X template hipError_t launch_dma<DT, 256, 128, 128, 64, 3, 1>(GemmArgs, bool, bool, int64_t, hipStream_t); \
+  X template hipError_t launch_dma<DT, 128, 256, 64, 128, 3, 1>(GemmArgs, bool, bool, int64_t, hipStream_t); \
+  X template hipError_t launch_dma<DT, 128, 128, 64, 64, 4, 1>(GemmArgs, bool, bool, int64_t, hipStream_t); \
+  X template hipError_t launch_persistent<DT, 128, 128, 64, 64, 2>(GemmArgs, bool, bool, hipStream_t); \
+  X template hipError_t launch_persistent<DT, 64, 128, 32, 64, 3>(GemmArgs, bool, bool, hipStream_t);
+#ifndef MPX_GEMM_STAGED_SOURCE
+MPX_GEMM_STAGED(extern, MPX_F16)
+MPX_GEMM_STAGED(extern, MPX_BF16)
+#endif
+#ifndef MPX_GEMM_FORCED_SOURCE
+MPX_GEMM_FORCED(extern, MPX_F16)
+MPX_GEMM_FORCED(extern, MPX_BF16)
+#endif
+
 // Tile configurations (the value of mpx_gemm_set_config):
-//   1  register-staged 64 x 64, 4 waves          (any operands)
-//   2  register-staged 128 x 128, 8 waves        (16-byte aligned operands)
+//   1  register-staged 64 x 64, 4 waves of 32 x 32    (any operands)
+//   2  register-staged 128 x 128, 4 waves of 64 x 64  (any operands)
 //   3  direct-to-LDS 256 x 256, 4 waves, 2 stages
 //   4  direct-to-LDS 256 x 128, 4 waves, 3 stages
 //   5  direct-to-LDS 128 x 256, 4 waves, 3 stages
@@ -1268,7 +1237,7 @@ static int choose_config(const GemmArgs& g, bool vec, bool ak, bool bk, int64_t 
   if (f == 9 && dma && ak) return 9;
   if ((f == 10 || f == 11) && dma && ak) return g.splits == 1 && nbatch == 1 ? f : (f == 10 ? 7 : 9);
   if (f >= 3 && f <= 7 && dma) return f;
-  if (f == 1 || (f == 2 && vec)) return f;
+  if (f == 1 || f == 2) return f;
   if (small && (g.M <= 32 || g.N <= 32 || g.K <= 32)) return 8;
   if (g.M <= 64 || g.N <= 64) return 1;
   // (the persistent forms 10 and 11 are 1-5% faster on a product alone, but
@@ -1276,7 +1245,7 @@ static int choose_config(const GemmArgs& g, bool vec, bool ak, bool bk, int64_t 
   // weight-gradient stream of the training step cannot interleave: the ViT
   // steps ran 2-4% slower with them)
   if (dma) return ak && prefer_64x128(g, nbatch) ? 9 : 7;
-  return vec ? 2 : 0;
+  return 2;
 }
 
 // ----------------------------------------------------------- skinny GEMMs --
@@ -1334,15 +1303,17 @@ static hipError_t launch_small(const GemmArgs& g, bool ak, bool bk, hipStream_t 
 
 // ak: A is k-major; bk: B is k-major.  A call with g.db set (a weight
 // gradient whose bias gradient is wanted) gets it from the GEMM when the
-// chosen kernel can sum it (the two-stage 128 x 128 direct-to-LDS kernel
-// with both operands mn-major); *db_fused tells the caller whether it did,
+// chosen kernel can sum it (the two-stage 128 x 128 kernels, and 64 x 64
+// ones without split-K: the split-K partials are laid out for 128-wide tile
+// columns); *db_fused tells the caller whether it did,
 // and otherwise the caller computes the column sums itself.
 template <int DT>
 static hipError_t run_gemm(GemmArgs g, bool ak, bool bk, int64_t nbatch, hipStream_t s,
                            bool* db_fused) {
   const bool vec = aligned_vec(g.A, g.lda, g.sA0, g.sA1) && aligned_vec(g.B, g.ldb, g.sB0, g.sB1);
   const int cfg = choose_config(g, vec, ak, bk, nbatch);
-  const bool fuse = g.db && cfg == 7 && !ak && !bk && nbatch == 1 && (g.splits == 1 || g.dbp);
+  const bool fuse = g.db && (cfg == 7 || cfg == 2 || (cfg == 1 && g.splits == 1)) && !ak && !bk &&
+                    nbatch == 1 && (g.splits == 1 || g.dbp);
   if (db_fused) *db_fused = fuse;
   if (!fuse) {
     g.db = nullptr;
@@ -1350,8 +1321,8 @@ static hipError_t run_gemm(GemmArgs g, bool ak, bool bk, int64_t nbatch, hipStre
   }
   switch (cfg) {
     case 8: return launch_small<DT>(g, ak, bk, s);
-    case 1: return launch_cfg<DT, 64, 64, 32, 32>(g, ak, bk, vec, nbatch, s);
-    case 2: return launch_cfg<DT, 128, 128, 64, 32, 64, 4>(g, ak, bk, vec, nbatch, s);
+    case 1: return launch_staged<DT, 64, 64, 32, 32>(g, ak, bk, nbatch, s);
+    case 2: return launch_staged<DT, 128, 128, 64, 64>(g, ak, bk, nbatch, s);
     case 3: return launch_dma<DT, 256, 256, 128, 128, 2, 1>(g, ak, bk, nbatch, s);
     case 4: return launch_dma<DT, 256, 128, 128, 64, 3, 1>(g, ak, bk, nbatch, s);
     case 5: return launch_dma<DT, 128, 256, 64, 128, 3, 1>(g, ak, bk, nbatch, s);
@@ -1360,8 +1331,7 @@ static hipError_t run_gemm(GemmArgs g, bool ak, bool bk, int64_t nbatch, hipStre
     case 9: return launch_dma<DT, 64, 128, 32, 64, 2, 3>(g, ak, bk, nbatch, s);
     case 10: return launch_persistent<DT, 128, 128, 64, 64, 2>(g, ak, bk, s);
     case 11: return launch_persistent<DT, 64, 128, 32, 64, 3>(g, ak, bk, s);
-    default:  // unaligned operands (rare: odd leading dimensions)
-      return launch_cfg<DT, 128, 128, 64, 64>(g, ak, bk, vec, nbatch, s);
+    default: return hipErrorInvalidValue;
   }
 }
 

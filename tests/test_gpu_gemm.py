@@ -523,3 +523,67 @@ def test_gemm_batched_f32(tr):
     bound = ulp(ref, "f32") + 2.0 * K * 2.0 ** -24 * np.matmul(np.abs(opa).astype(np.float64),
                                                                np.abs(opb).astype(np.float64))
     assert_within(got, ref, bound, "batched f32")
+
+
+@pytest.mark.parametrize("config", [0, 1, 2])
+@pytest.mark.parametrize("tr", [(0, 1), (0, 0), (1, 0), (1, 1)], ids=str)
+@pytest.mark.parametrize("mnk", [(65, 67, 9), (130, 129, 63), (129, 200, 65), (40, 136, 588), (64, 128, 5),
+                                 (7, 70, 130), (70, 7, 133), (257, 131, 191)], ids=lambda s: "x".join(map(str, s)))
+def test_unaligned_operands(config, tr, mnk):
+    """Operands whose rows are not 16-byte aligned, every layout, at the edges
+    of the tiles and of the 8-value loads (extents of 5 to 9, one past and one
+    short of a tile): rows padded with NaN, which must not reach a result, and
+    output rows padded with a mark, which must stay."""
+    M, N, K = mnk
+    a, b = _rand((M, K), "bf16", 61), _rand((N, K), "bf16", 62, 0.1)
+    ta = to_dev_half(np.ascontiguousarray(a.T) if tr[0] else a, "bf16")
+    tb = to_dev_half(b if tr[1] else np.ascontiguousarray(b.T), "bf16")
+    pad = lambda t, n: torch.nn.functional.pad(t, (0, n), value=float("nan")).contiguous()  # noqa: E731
+    pa, pb = pad(ta, 3), pad(tb, 5)
+    pc = torch.full((M, N + 1), 7.0, dtype=ta.dtype, device="cuda")
+    mx.mpx_gemm_set_config(config)
+    try:
+        mx.mpx_gemm_batched(tr[0], tr[1], M, N, K, 1, 1, pa.data_ptr(), pa.shape[1], 0, 0, pb.data_ptr(),
+                            pb.shape[1], 0, 0, pc.data_ptr(), N + 1, 0, 0, mx.DTYPES["bf16"], _s())
+    finally:
+        mx.mpx_gemm_set_config(0)
+    ref = Policy("bf16").gemm(a, b.T)
+    got = to_host(pc)
+    assert_within(got[:, :N], ref, gemm_bound(a, b.T, ref, "bf16", K), "C")
+    assert np.all(got[:, N] == 7.0)
+
+
+@pytest.mark.parametrize("mnk", [(130, 200, 588), (77, 130, 68), (2100, 75, 133)], ids=lambda s: "x".join(map(str, s)))
+def test_linear_epilogues_with_unaligned_rows(mnk):
+    """Bias + GELU, residual, GELU' and the bias gradient on ragged, unaligned
+    outputs, each against the oracle."""
+    M, N, K = mnk
+    fmt, pol, dt = "f16", Policy("f16"), mx.DTYPES["f16"]
+    x, w, b, r = (_rand(s, fmt, 70 + i, d) for i, (s, d) in enumerate((((M, K), 1.0), ((N, K), 0.05), ((N,), 0.5),
+                                                                      ((M, N), 1.0))))
+    dy, xpre = _rand((M, N), fmt, 75, 0.1), _rand((M, K), fmt, 76)
+    tx, tw, tb, tr_, tdy, txp = (to_dev_half(a, fmt) for a in (x, w, b, r, dy, xpre))
+    y, pre, yr = _empty((M, N), fmt), _empty((M, N), fmt), _empty((M, N), fmt)
+    p = lambda t: t.data_ptr()  # noqa: E731
+    mx.mpx_linear_fwd(p(tx), p(tw), p(tb), None, p(y), p(pre), M, N, K, dt, mx.MPX_ACT_GELU_TANH, _s())
+    mx.mpx_linear_fwd(p(tx), p(tw), p(tb), p(tr_), p(yr), None, M, N, K, dt, mx.MPX_ACT_NONE, _s())
+    ref = ops.linear_fwd(pol, x, w, b)
+    bound = gemm_bound(x, w.T, ref, fmt, K)
+    gpre = to_host(pre)
+    assert_within(gpre, ref, bound, "pre-activation")
+    g_ref = ops.gelu_fwd(pol, gpre)
+    assert_within(to_host(y), g_ref, ulp(g_ref, fmt), "gelu")
+    r_ref = pol.R(ref + r)
+    assert_within(to_host(yr), r_ref, bound + ulp(r_ref, fmt), "residual")
+    gdx, gdw, gdb = _empty((M, K), fmt), _empty((N, K), fmt), _empty((N,), fmt)
+    n = mx.mpx_linear_bwd_workspace(M, N, K)
+    ws = torch.zeros(n, dtype=torch.uint8, device="cuda")
+    bad = torch.zeros(1, dtype=torch.int32, device="cuda")
+    mx.mpx_linear_bwd(p(tx), p(tw), p(tdy), p(txp), mx.MPX_ACT_GELU_TANH, p(gdx), p(gdw), p(gdb), M, N, K, dt, p(ws),
+                      n, p(bad), _s())
+    rdx, rdw, rdb = ops.linear_bwd(pol, x, w, dy)
+    assert_within(to_host(gdw), rdw, gemm_bound(dy.T, x, rdw, fmt, M), "dW")
+    assert_within(to_host(gdb), rdb, ulp(rdb, fmt) + 2 * M * 2.0 ** -24 * np.abs(dy).sum(0), "db")
+    ref = ops.gelu_bwd(pol, xpre, rdx)
+    assert_within(to_host(gdx), ref, 1.13 * gemm_bound(dy, w, rdx, fmt, N) + ulp(ref, fmt), "dX through gelu'")
+    assert int(bad.item()) == 0
