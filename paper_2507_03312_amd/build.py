@@ -18,7 +18,7 @@ INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(PKG, "libmpx.so")
 BUILD_DIR = os.path.join(PKG, "_build")
 SOURCES = ["gemm_f16.hip", "gemm_bf16.hip", "gemm_staged_f16.hip", "gemm_staged_bf16.hip",
-           "gemm_forced_f16.hip", "gemm_forced_bf16.hip", "support.hip", "attention.hip", "sweep.hip",
+           "gemm_wide_f16.hip", "gemm_wide_bf16.hip", "support.hip", "attention.hip", "sweep.hip",
            "gemm.hip", "gemm_f32.hip", "support_f32.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")

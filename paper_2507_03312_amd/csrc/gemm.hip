@@ -28,22 +28,35 @@ static GemmArgs base_args() {
 
 // split-K plan for a reduction of length K over an MxN output (the weight
 // gradients, whose outputs have far fewer 128 x 128 tiles than the chip has
-// workgroup slots): enough splits for one workgroup per CU (256 tiles x
-// splits, rounded up), at most 16 and at least 1024 reduction values each.
-// The weight gradients run on a second stream beside the critical path, so
-// filling the 512 slots of two workgroups per CU (the earlier rule) bought
-// latency no one waited for with more float32 partials to write and reduce:
-// this rule measured ViT-B +1.2% and ViT-S +2.0% on one box and leaves the
-// one-block model's splits as they were (the 1024-value floor binds there);
-// 192 slots: ViT-S -1.5%; at least 2048 values per split: ViT-S -2.3%, one
-// block -3%; rounding 256 / tiles down left the ViT-B MLP gradients unsplit:
-// -7%.
+// workgroup slots): the split count of least estimated time, with at most 512
+// workgroups (two per CU), 16 splits and at least 1024 reduction values each.
+// A k tile of 64 takes 0.74 us with one workgroup per CU and 1.07 us with two
+// (256 + 1 workgroups cost as much as 512; a third round as much again), and
+// each split's float32 partials cost their write and read, 8 bytes per output:
+// 1.8 us per million outputs alone, charged as 3.5 because the partials also
+// push the operands of the neighbouring kernels out of the caches (16640 x 1536
+// x 384 in 14 splits instead of 7: the product and its reduction alone 47.4 ->
+// 43.9 us, the MLP layers around it 2% slower).  Against one workgroup per CU,
+// rounded up, the rule before: 12608 x 2304 x 768 3 -> 4 splits 82 -> 69 us,
+// 12608 x 3072 x 768 2 -> 3 splits 93 -> 78 us with operands from HBM; the
+// ViT-B step, where these run beside the critical path, 10.98 -> 10.55 ms.
 static int choose_splits(int64_t M, int64_t N, int64_t K) {
   const int64_t tiles = ((M + 127) / 128) * ((N + 127) / 128);
-  int64_t s = (256 + tiles - 1) / tiles;
-  s = std::min<int64_t>(s, 16);
-  s = std::min<int64_t>(s, std::max<int64_t>(1, K / 1024));
-  return (int)std::max<int64_t>(s, 1);
+  const int64_t most = std::min<int64_t>({512 / tiles, 16, K / 1024});
+  int best = 1;
+  double least = 0.0;
+  for (int64_t s = 1; s <= std::max<int64_t>(most, 1); ++s) {
+    // k tiles x their time in the full rounds and in the last one
+    const int64_t wgs = tiles * s, full = wgs / 512, last = (wgs % 512 + 255) / 256;
+    const double k_tile = 1.07 * (double)full + (last == 2 ? 1.07 : last == 1 ? 0.74 : 0.0);
+    const double t = (double)((K + 64 * s - 1) / (64 * s)) * k_tile +
+                     (s > 1 ? 3.0 + 3.5e-6 * (double)(s * M * N) : 0.0);
+    if (least == 0.0 || t < least) {
+      least = t;
+      best = (int)s;
+    }
+  }
+  return best;
 }
 
 // split-K plan of a reduction of length Mr over an N x K weight gradient:

@@ -122,8 +122,9 @@ typedef u32x4 u32x4_any __attribute__((aligned(2)));
 // that straddle its last column go one value at a time.
 // pf (nullable): the wave's GELU' or residual operand rows, already loaded
 // in the row layout (16 bytes of row (lane >> 3) + 8 t per entry t).
-template <int DT, int TM, int TN, int E, bool EDGE = false>
-__device__ __forceinline__ void gemm_epilogue_lds(const GemmArgs& g, const f32x16 (&acc)[TM][TN],
+// J0: first of the TN accumulator columns handled (of TNA).
+template <int DT, int TM, int TN, int E, bool EDGE = false, int J0 = 0, int TNA = TN>
+__device__ __forceinline__ void gemm_epilogue_lds(const GemmArgs& g, const f32x16 (&acc)[TM][TNA],
                                                   int64_t mw, int64_t nw, int lane, int64_t offC,
                                                   uint16_t* lds, const u32x4* pf = nullptr, int mv = 0,
                                                   int nv = 0) {
@@ -161,7 +162,7 @@ __device__ __forceinline__ void gemm_epilogue_lds(const GemmArgs& g, const f32x1
         const int row = 32 * i + r32;
         uint16_t h[4];
 #pragma unroll
-        for (int c = 0; c < 4; ++c) h[c] = f2h<DT>(acc[i][j][4 * q + c] + b[c]);
+        for (int c = 0; c < 4; ++c) h[c] = f2h<DT>(acc[i][J0 + j][4 * q + c] + b[c]);
         *reinterpret_cast<u32x2*>(lds + row * PITCH + col) =
             u32x2{h[0] | ((uint32_t)h[1] << 16), h[2] | ((uint32_t)h[3] << 16)};
       });
@@ -204,9 +205,31 @@ __device__ __forceinline__ void gemm_epilogue_lds(const GemmArgs& g, const f32x1
         if (c < nc) p[c] = h[c];
     }
   };
+  // the GELU' or residual rows, all in flight before the first store (a load
+  // behind a store that may alias it would wait for it: one memory latency
+  // per step)
+  constexpr int STEPS = 32 * TM / RPT;
+  constexpr bool kOp = E != EPI_GENERIC && (E & (EPI_DACT | EPI_RESID)) != 0;
+  u32x4 op[kOp ? STEPS : 1];
+  if constexpr (kOp) {
+    const uint16_t* src = (E & EPI_DACT) ? dact : res;
+    const int64_t ld_op = (E & EPI_DACT) ? ldc : g.ldr;
+#pragma unroll
+    for (int t = 0; t < STEPS; ++t) {
+      const int row = lane / LPR + RPT * t;
+      if (!EDGE && pf) op[t] = pf[t];
+      else if (!EDGE || (row < mv && nc == 8))
+        op[t] = *reinterpret_cast<const vec*>(src + (off_t)(row * ld_op + c8));
+      else op[t] = u32x4{0u, 0u, 0u, 0u};
+    }
+  }
+  auto operand8 = [&](int t, const uint16_t* p, uint16_t (&h)[8]) {
+    if (kOp && nc == 8) h8(op[kOp ? t : 0], h);
+    else load8(p, h);
+  };
   int bad = 0;
 #pragma unroll
-  for (int t = 0; t < 32 * TM / RPT; ++t) {
+  for (int t = 0; t < STEPS; ++t) {
     const int row = lane / LPR + RPT * t;
     const u32x2 w0 = *reinterpret_cast<const u32x2*>(lds + row * PITCH + c8);
     const u32x2 w1 = *reinterpret_cast<const u32x2*>(lds + row * PITCH + c8 + 4);
@@ -223,15 +246,13 @@ __device__ __forceinline__ void gemm_epilogue_lds(const GemmArgs& g, const f32x1
     }
     if (do_dact) {
       uint16_t da[8];
-      if (!EDGE && pf) h8(pf[t], da);
-      else load8(dact + off, da);
+      operand8(t, dact + off, da);
 #pragma unroll
       for (int c = 0; c < 8; ++c) h[c] = f2h<DT>(h2f<DT>(h[c]) * gelu_tanh_grad(h2f<DT>(da[c])));
     }
     if (do_res) {
       uint16_t rv[8];
-      if (!EDGE && pf) h8(pf[t], rv);
-      else load8(res + (off_t)(row * g.ldr + c8), rv);
+      operand8(t, res + (off_t)(row * g.ldr + c8), rv);
 #pragma unroll
       for (int c = 0; c < 8; ++c) h[c] = f2h<DT>(h2f<DT>(h[c]) + h2f<DT>(rv[c]));
     }
@@ -250,115 +271,32 @@ __device__ __forceinline__ void gemm_epilogue_lds(const GemmArgs& g, const f32x1
   if (do_count) add_nonfinite(g.nonfinite, bad);
 }
 
-// Generic epilogue shared by the GEMM kernels: any tile, any operand
-// alignment, split-K partials.  The wave's TM x TN accumulator blocks of
-// 32 x 32 start at output row mw and column nw.  Two accumulator layouts:
-//   TRANS = false (C = A B^T blocks): lane l holds column l % 32 and 4 runs of
-//     4 consecutive rows; a 4x4 transpose across lane quads (two DPP
-//     butterfly exchanges) turns each run into 4 consecutive columns of one row;
-//   TRANS = true (the MFMA operands swapped, C^T blocks): lane l already holds
-//     row l % 32, columns 8 q + 4 (l / 32) + (0..3) for q = 0..3.
-// Either way bias / residual / activation inputs are read and outputs written
-// 4 elements (8 bytes; 16 for float partials) at a time.
-template <int DT, int TM, int TN, bool TRANS = false>
-__device__ __forceinline__ void gemm_epilogue(const GemmArgs& g, const f32x16 (&acc)[TM][TN],
-                                              int64_t mw, int64_t nw, int lane, int split,
-                                              int64_t offC) {
-  const int q4 = lane & 3;
-  // run q of block (i, j): its 4 values, output row and first column
-  auto run = [&](const f32x16& a, int i, int j, int q, float (&v)[4], int64_t& m, int64_t& n) {
-#pragma unroll
-    for (int c = 0; c < 4; ++c) v[c] = a[4 * q + c];
-    if constexpr (TRANS) {
-      m = mw + i * 32 + (lane & 31);
-      n = nw + j * 32 + 8 * q + 4 * (lane >> 5);
-    } else {
-      quad_transpose(v, q4);
-      m = mw + i * 32 + 8 * q + 4 * (lane >> 5) + q4;
-      n = nw + j * 32 + 4 * ((lane & 31) >> 2);
-    }
-  };
-  auto al8 = [](const void* p) { return (reinterpret_cast<uintptr_t>(p) & 7u) == 0; };
-  if (g.splits > 1) {
-    float* W = g.ws + (int64_t)split * g.M * g.N;
-    const bool v16 = g.N % 4 == 0 && (reinterpret_cast<uintptr_t>(W) & 15u) == 0;
-    static_for<TM>([&](auto i) {
-      static_for<TN>([&](auto j) {
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          float v[4];
-          int64_t m, n;
-          run(acc[i][j], i, j, q, v, m, n);
-          if (m < g.M && n < g.N) {
-            float* out = W + m * g.N + n;
-            if (v16 && n + 4 <= g.N) *reinterpret_cast<f32x4*>(out) = f32x4{v[0], v[1], v[2], v[3]};
-            else
-#pragma unroll
-              for (int c = 0; c < 4; ++c)
-                if (n + c < g.N) out[c] = v[c];
-          }
-        }
-      });
-    });
-    return;
-  }
-  uint16_t* C = g.C + offC;
-  const bool v8 = g.ldc % 4 == 0 && al8(C) && (!g.pre || al8(g.pre)) && (!g.dact || al8(g.dact)) &&
-                  (!g.resid || (al8(g.resid) && g.ldr % 4 == 0)) && (!g.bias || al8(g.bias));
-  auto ld4 = [&](const uint16_t* p, bool vec, int nv, uint16_t (&d)[4]) {
-    if (vec) {
-      const u32x2 w = *reinterpret_cast<const u32x2*>(p);
-      d[0] = (uint16_t)(w.x & 0xFFFFu);
-      d[1] = (uint16_t)(w.x >> 16);
-      d[2] = (uint16_t)(w.y & 0xFFFFu);
-      d[3] = (uint16_t)(w.y >> 16);
-    } else {
-#pragma unroll
-      for (int c = 0; c < 4; ++c) d[c] = c < nv ? p[c] : (uint16_t)0;
-    }
-  };
-  auto st4 = [&](uint16_t* p, bool vec, int nv, const uint16_t (&d)[4]) {
-    if (vec) {
-      *reinterpret_cast<u32x2*>(p) = u32x2{d[0] | ((uint32_t)d[1] << 16), d[2] | ((uint32_t)d[3] << 16)};
-    } else {
-#pragma unroll
-      for (int c = 0; c < 4; ++c)
-        if (c < nv) p[c] = d[c];
-    }
-  };
-  int bad = 0;
+// Split-K: the wave's float32 sums (accumulators hold C^T blocks: lane l has
+// row l % 32, columns 8 q + 4 (l / 32) + (0..3) for q = 0..3) go to the
+// split's partial matrix in the workspace, 16 bytes at a time where its rows
+// allow.
+template <int TM, int TN>
+__device__ __forceinline__ void gemm_partials(const GemmArgs& g, const f32x16 (&acc)[TM][TN], int64_t mw,
+                                              int64_t nw, int lane, int split) {
+  float* W = g.ws + (int64_t)split * g.M * g.N;
+  const bool v16 = g.N % 4 == 0 && (reinterpret_cast<uintptr_t>(W) & 15u) == 0;
   static_for<TM>([&](auto i) {
     static_for<TN>([&](auto j) {
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        float v[4];
-        int64_t m, n;
-        run(acc[i][j], i, j, q, v, m, n);
-        const int nv = (int)max<int64_t>(0, min<int64_t>(4, g.N - n));
-        if (m >= g.M || nv == 0) continue;
-        const bool vec = v8 && nv == 4;
-        uint16_t bias[4] = {0, 0, 0, 0}, h[4], da[4], res[4];
-        if (g.bias) ld4(g.bias + n, vec, nv, bias);
-        if (g.dact) ld4(g.dact + m * g.ldc + n, vec, nv, da);
-        if (g.resid) ld4(g.resid + m * g.ldr + n, vec, nv, res);
+        const int64_t m = mw + i * 32 + (lane & 31), n = nw + j * 32 + 8 * q + 4 * (lane >> 5);
+        const f32x4 v = {acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
+        if (m < g.M && n < g.N) {
+          float* out = W + m * g.N + n;
+          if (v16) *reinterpret_cast<f32x4*>(out) = v;  // N % 4 == 0: the 4 columns exist
+          else
 #pragma unroll
-        for (int c = 0; c < 4; ++c) h[c] = f2h<DT>(v[c] + (g.bias ? h2f<DT>(bias[c]) : 0.0f));
-        if (g.pre) st4(g.pre + m * g.ldc + n, vec, nv, h);
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-          uint16_t o = h[c];
-          if (g.act == MPX_ACT_GELU_TANH) o = f2h<DT>(gelu_tanh(h2f<DT>(o)));
-          if (g.dact) o = f2h<DT>(h2f<DT>(o) * gelu_tanh_grad(h2f<DT>(da[c])));
-          if (g.resid) o = f2h<DT>(h2f<DT>(o) + h2f<DT>(res[c]));
-          h[c] = o;
+            for (int c = 0; c < 4; ++c)
+              if (n + c < g.N) out[c] = v[c];
         }
-#pragma unroll
-        for (int c = 0; c < 4; ++c) bad += (c < nv && h_nonfinite<DT>(h[c])) ? 1 : 0;
-        st4(C + m * g.ldc + n, vec, nv, h);
       }
     });
   });
-  if (g.nonfinite) add_nonfinite(g.nonfinite, bad);
 }
 
 // ------------------------------------------------- direct-to-LDS kernel --
@@ -404,12 +342,12 @@ __device__ __forceinline__ void wait_vmcnt() {
 
 // Position of 16-byte chunk c of row r (k-major: output row of 64 k; mn-major:
 // k row of ROWS outputs) within the row in LDS; its own inverse.  An mn-major
-// row of 64 outputs spans half the banks, so there rows 2 and 3 of each four
-// move to the other half of their row.
+// row of 64 (192) outputs spans half (one and a half times) the banks, so there
+// rows 2 and 3 of each four move to the other half of each 128 bytes.
 template <int ROWS, bool KMAJ>
 __device__ __forceinline__ int dma_chunk(int r, int c) {
   if constexpr (KMAJ) return c ^ ((r >> 1) & 7);
-  else if constexpr (ROWS == 64) return c ^ (4 * ((r >> 1) & 1));
+  else if constexpr (ROWS % 128 == 64) return c ^ (4 * ((r >> 1) & 1));
   else return c ^ (4 * (r & 3));
 }
 
@@ -420,7 +358,7 @@ struct DmaOperand {
   static constexpr int BLOCKS = ROWS / 8;  // 1 KiB copies per stage
   static constexpr int Q = BLOCKS / NWAVES;
   static_assert(BLOCKS % NWAVES == 0, "copies do not split evenly over the waves");
-  static_assert(KMAJ || ROWS == 64 || ROWS == 128 || ROWS == 256, "mn-major tile widths");
+  static_assert(KMAJ || ROWS == 64 || ROWS == 128 || ROWS == 192 || ROWS == 256, "mn-major tile widths");
   uint32_t off[Q];  // per-lane byte offsets of the copies, relative to the tile base
   int64_t step;     // bytes from one k tile to the next
 
@@ -435,13 +373,13 @@ struct DmaOperand {
         off[q] = (uint32_t)(min(r, rv - 1) * ld * 2 + c * 16);
       }
     } else {
-      constexpr int CH = ROWS / 8;   // 16-byte chunks per k row
-      constexpr int RPB = 64 / CH;   // k rows per 1 KiB copy
+      constexpr int CH = ROWS / 8;  // 16-byte chunks per k row
       step = 64 * ld * 2;
 #pragma unroll
       for (int q = 0; q < Q; ++q) {
-        const int kr = RPB * (wave + NWAVES * q) + lane / CH;
-        const int c = dma_chunk<ROWS, false>(kr, lane % CH);
+        const int at = 64 * (wave + NWAVES * q) + lane;  // the tile's chunk this lane copies
+        const int kr = at / CH;
+        const int c = dma_chunk<ROWS, false>(kr, at % CH);
         off[q] = (uint32_t)(kr * ld * 2 + (8 * c < rv ? 16 * c : 0));
       }
     }
@@ -466,61 +404,77 @@ struct DmaOperand {
 // copies would have filled, so the fragment reads are the same.  Vectors that
 // would reach past the end of their row (the last k of a k-major row, the
 // last output of an mn-major one) are loaded ending at the row's last element
-// and shifted down, with zeros behind: no access leaves the matrix.
-// Extents below 8 (no whole vector in a row) load one value at a time.
-template <int ROWS, bool KMAJ, int NWAVES>
+// and shifted down, with zeros behind: no access leaves the matrix.  Two k
+// tiles are in flight (the register sets v[0] and v[1]).
+// ANY: rows of fewer than 8 values (no whole vector fits) or strides past the
+// 32-bit lane offsets: one value at a time with 64-bit addresses; a type of
+// its own, because a branch around the loads makes them wait.
+template <int ROWS, bool KMAJ, int NWAVES, bool ANY>
 struct StagedOperand {
   static constexpr int BLOCKS = ROWS / 8, Q = BLOCKS / NWAVES;
   static_assert(BLOCKS % NWAVES == 0, "blocks do not split evenly over the waves");
   static constexpr int CH = KMAJ ? 8 : ROWS / 8;
-  u32x4 v[Q];
-  const uint16_t* base;  // tile's first element at the split's first k
+  static constexpr int RSTEP = 64 / CH * NWAVES;  // rows from one vector of a lane to its next
+  u32x4 v[2][Q];
+  uint32_t off[Q];  // lane offsets (bytes) from 8 elements before the tile's first
   int64_t ld;
-  int c8;    // first k (k-major) or output (mn-major) of the lane's vectors within the tile
-  int r0;    // output row (k-major) or k row (mn-major) of the lane's vector 0
-  int rv;    // rows of the matrix from the tile's first on
-  int krem;  // reduction values from the loaded tile's first on
-  bool tiny;
+  int c8;       // first k (k-major) or output (mn-major) of the lane's vectors within the tile
+  int r0;       // output row (k-major) or k row (mn-major) of the lane's vector 0
+  int rv;       // rows (k-major) or outputs (mn-major) of the matrix from the tile's first on
+  int krem[2];  // reduction values from the loaded tile's first on
 
-  // extent: length of a row of the operand's storage (K or the output count)
-  __device__ __forceinline__ void init(const uint16_t* base_, int64_t ld_, int64_t rows_left, int64_t extent,
-                                       int wave, int lane) {
-    base = base_;
+  __device__ __forceinline__ void init(int64_t ld_, int64_t left, int wave, int lane) {
     ld = ld_;
-    rv = (int)min<int64_t>(rows_left, 1 << 20);
-    tiny = extent < 8;
-    const int blk = 64 / CH;  // rows per 1 KiB block
-    r0 = blk * wave + lane / CH;
+    rv = (int)min<int64_t>(left, 1 << 20);
+    r0 = 64 / CH * wave + lane / CH;
     c8 = 8 * dma_chunk<ROWS, KMAJ>(r0, lane % CH);
-  }
-  __device__ __forceinline__ void load(int64_t k0, int krem_) {
-    krem = krem_;
-    const int n = KMAJ ? krem : rv;  // elements from the tile's first on in the vector's direction
-    const int start = min(c8, n - 8);
 #pragma unroll
     for (int q = 0; q < Q; ++q) {
-      const int r = min(r0 + 64 / CH * NWAVES * q, (KMAJ ? rv : krem) - 1);
-      const uint16_t* row = KMAJ ? base + (int64_t)r * ld + k0 : base + (k0 + r) * ld;
-      if (!tiny) {
-        v[q] = *reinterpret_cast<const u32x4_any*>(row + start);
-      } else {
+      const int r = r0 + RSTEP * q;
+      off[q] = 16 + (KMAJ ? (uint32_t)(min(r, rv - 1) * ld * 2) + 2 * c8
+                          : (uint32_t)(r * ld * 2) + (uint32_t)(2 * min(c8, rv - 8)));
+    }
+  }
+  // tile: its first element; kr: reduction values from there on (>= 1)
+  template <int P>
+  __device__ __forceinline__ void load(const uint16_t* tile, int kr) {
+    krem[P] = kr;
+    if constexpr (ANY) {
+      const int n = KMAJ ? kr : rv;
+#pragma unroll
+      for (int q = 0; q < Q; ++q) {
+        const uint16_t* row = tile + (int64_t)min(r0 + RSTEP * q, (KMAJ ? rv : kr) - 1) * ld;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           const uint32_t lo = c8 + 2 * e < n ? row[c8 + 2 * e] : (uint16_t)0;
           const uint32_t hi = c8 + 2 * e + 1 < n ? row[c8 + 2 * e + 1] : (uint16_t)0;
-          v[q][e] = lo | (hi << 16);
+          v[P][q][e] = lo | (hi << 16);
         }
+      }
+    } else {
+      const uint8_t* base = reinterpret_cast<const uint8_t*>(tile - 8);  // never accessed itself
+      const int back = KMAJ ? 2 * max(0, c8 + 8 - kr) : 0;  // k-major: how far past the row's end
+#pragma unroll
+      for (int q = 0; q < Q; ++q) {
+        uint32_t o = off[q];
+        if (kr < 64) {  // uniform: the last k tile
+          if (KMAJ) o -= back;
+          else o -= (uint32_t)(max(0, r0 + RSTEP * q - (kr - 1)) * ld * 2);
+        }
+        v[P][q] = *reinterpret_cast<const u32x4_any*>(base + o);
       }
     }
   }
+  template <int P>
   __device__ __forceinline__ void store(uint8_t* lds, int wave, int lane) {
-    const bool whole = (KMAJ ? krem : rv) >= (KMAJ ? 64 : ROWS) || tiny;
-    const int sh = c8 - min(c8, (KMAJ ? krem : rv) - 8);
+    const int n = KMAJ ? krem[P] : rv;
+    const bool whole = ANY || n >= (KMAJ ? 64 : ROWS);
+    const int sh = c8 - min(c8, n - 8);
 #pragma unroll
     for (int q = 0; q < Q; ++q) {
-      u32x4 x = v[q];
+      u32x4 x = v[P][q];
       if (!whole) x = shr_halves(x, sh);
-      if (!KMAJ && r0 + 64 / CH * NWAVES * q >= krem) x = u32x4{0u, 0u, 0u, 0u};
+      if (!KMAJ && r0 + RSTEP * q >= krem[P]) x = u32x4{0u, 0u, 0u, 0u};
       *reinterpret_cast<u32x4*>(lds + 1024 * (wave + NWAVES * q) + 16 * lane) = x;
     }
   }
@@ -569,8 +523,6 @@ struct FragReader {
   }
 };
 
-// OCC: waves per SIMD the register budget is sized for.  E: the epilogue
-// variant of whole tiles (EPI_GENERIC: always the generic epilogue).
 // Sum of the 8 half values of an MFMA operand fragment, in a fixed pairwise order.
 template <int DT>
 __device__ __forceinline__ float frag_sum8(const uint4& f) {
@@ -581,6 +533,25 @@ __device__ __forceinline__ float frag_sum8(const uint4& f) {
   return (p[0] + p[1]) + (p[2] + p[3]);
 }
 
+// One BM x BN output tile per workgroup, waves of WM x WN, k tiles of 64 in
+// two LDS stages.
+//
+// What bounds it: with random operands and every CU busy the chip runs at its
+// power limit (256 x 256 tiles: 1.65 us per k tile, 1.3 PFLOP/s; 1.2 us with
+// operands of zeros), so the shape of the tiles matters through the bytes
+// moved per MFMA, the rounds a tile count needs, and what each tile costs
+// before and after its k loop.  The loop itself has no wait at its top: the
+// barrier that publishes k tile kt + 1, and frees the stage of tile kt,
+// stands before the last of tile kt's four k steps of 16, whose MFMAs cover the
+// fragment reads of tile kt + 1's first step; the copies of tile kt + 2 start
+// right behind it and have a whole k tile to land.  (With the barrier at the
+// top of each k tile, 128 x 128 tiles took 61.5 / 56.2 / 78.9 us forward at
+// 12608 x 2304 x 768, dX there and forward at 12608 x 3072 x 768 in bf16;
+// this loop 53.6 / 50.7 / 69.9.)
+//
+// OCC: waves per SIMD the register budget is sized for.  E: the epilogue
+// operations compiled in (EPI_GENERIC: taken from the arguments).
+//
 // DBS: also sum the rows of A over this workgroup's k range (the bias
 // gradient of a weight-gradient product; see GemmArgs::db).  The waves of
 // the left half of the tile (wn0 == 0) add up their A fragments as the MFMAs
@@ -593,30 +564,29 @@ __device__ __forceinline__ float frag_sum8(const uint4& f) {
 // partials with one wave, in a fixed order); without split-K column 0 sums
 // every k tile and writes db itself.
 //
-// STG: the operands go through registers (StagedOperand) instead of the
-// direct copies, with two stages; any alignment and any reduction length.
-// The loads of k tile kt + 2 are issued, and tile kt + 1 is written to the
-// other stage, ahead of the MFMAs of tile kt, so a load has a whole k step to
-// land.  Every tile takes the epilogue through LDS, which handles ragged
-// edges and unaligned rows there.  (One-value loads served these operands
+// STG (1; 2 for operands of StagedOperand's ANY form): the operands go
+// through registers (StagedOperand) instead of the direct copies: any
+// alignment and any reduction length.  Tile kt + 1 is written to the other
+// stage and the loads of tile kt + 3 are issued ahead of the MFMAs of tile kt,
+// so a load has two k tiles to land.  (One-value loads served these operands
 // before: 8415 x 768 x 588 in bf16 forward / dX / dW took 89 / 145 / 157 us.)
-template <int DT, int BM, int BN, int WM, int WN, int S, int OCC, bool AK, bool BKM, int E,
-          bool DBS = false, bool STG = false>
+template <int DT, int BM, int BN, int WM, int WN, int OCC, bool AK, bool BKM, int E, bool DBS = false,
+          int STG = 0>
 __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64)
 __attribute__((amdgpu_waves_per_eu(OCC, OCC)))
-void gemm_dma_kernel(GemmArgs g) {
+void gemm_tile_kernel(GemmArgs g) {
   constexpr int NWAVES = (BM / WM) * (BN / WN);
   constexpr int TM = WM / 32, TN = WN / 32;
   constexpr int A_BYTES = BM * 64 * 2, B_BYTES = BN * 64 * 2;
   constexpr int STAGE = A_BYTES + B_BYTES;
-  constexpr int L = (BM + BN) / 8 / NWAVES;  // copies per lane per stage
-  static_assert((S - 2) * L <= 63, "vmcnt range");
-  static_assert(!STG || S == 2, "two stages");
+  constexpr int L = (BM + BN) / 8 / NWAVES;  // copies per lane per k tile
   // LDS read instructions per k step (a k-major fragment is one 16-byte
-  // read, an mn-major one two transposing 8-byte reads), per MFMA
+  // read, an mn-major one two transposing 8-byte reads)
   constexpr int kReads = TM * (AK ? 1 : 2) + TN * (BKM ? 1 : 2);
-  constexpr int kReadsPerMfma = (kReads + TM * TN - 1) / (TM * TN);
-  __shared__ __attribute__((aligned(1024))) uint8_t smem[S * STAGE];
+  // the epilogue works on 64 columns of a wave at a time
+  constexpr int EC = WN < 64 ? WN : 64;
+  constexpr int EPI = NWAVES * WM * (EC + 4) * 2;
+  __shared__ __attribute__((aligned(1024))) uint8_t smem[2 * STAGE > EPI ? 2 * STAGE : EPI];
   const uint32_t lds0 = lds_u32(smem);
 
   const int tid = threadIdx.x;
@@ -644,20 +614,69 @@ void gemm_dma_kernel(GemmArgs g) {
 
   const uint16_t* Ab = g.A + offA + (AK ? m0 * g.lda + kbeg : kbeg * g.lda + m0);
   const uint16_t* Bb = g.B + offB + (BKM ? n0 * g.ldb + kbeg : kbeg * g.ldb + n0);
-  std::conditional_t<STG, StagedOperand<BM, AK, NWAVES>, DmaOperand<BM, AK, NWAVES>> da;
-  std::conditional_t<STG, StagedOperand<BN, BKM, NWAVES>, DmaOperand<BN, BKM, NWAVES>> db;
-  if constexpr (STG) {
-    da.init(Ab, g.lda, g.M - m0, AK ? g.K : g.M, wave, lane);
-    db.init(Bb, g.ldb, g.N - n0, BKM ? g.K : g.N, wave, lane);
+  std::conditional_t<STG != 0, StagedOperand<BM, AK, NWAVES, STG == 2>, DmaOperand<BM, AK, NWAVES>> da;
+  std::conditional_t<STG != 0, StagedOperand<BN, BKM, NWAVES, STG == 2>, DmaOperand<BN, BKM, NWAVES>> db;
+  if constexpr (STG != 0) {
+    da.init(g.lda, g.M - m0, wave, lane);
+    db.init(g.ldb, g.N - n0, wave, lane);
   } else {
     da.init(g.lda, (int)min<int64_t>(BM, g.M - m0), wave, lane);
     db.init(g.ldb, (int)min<int64_t>(BN, g.N - n0), wave, lane);
   }
+
+  const bool whole = g.full_epi && m0 + BM <= g.M && n0 + BN <= g.N;  // uniform over the workgroup
+  const int64_t mw = m0 + wm0, nw = n0 + wn0;
+  // A whole tile's GELU' or residual operand is loaded into registers before
+  // the first copies where they fit (the oldest loads, so the first tile's
+  // wait covers them): the epilogue then starts without a memory round trip.
+  constexpr bool kPF = STG == 0 && E != EPI_GENERIC && (E & (EPI_DACT | EPI_RESID)) != 0 && TN == 2 && TM <= 2;
+  u32x4 pf[kPF ? 4 * TM : 1];
+  if constexpr (kPF) {
+    if (whole) {
+      const int64_t ldp = (E & EPI_DACT) ? g.ldc : g.ldr;
+      const uint16_t* src = ((E & EPI_DACT) ? g.dact : g.resid) + (mw * ldp + nw);
+#pragma unroll
+      for (int t = 0; t < 4 * TM; ++t)
+        pf[t] = *reinterpret_cast<const u32x4*>(src + (uint32_t)(((lane >> 3) + 8 * t) * ldp + 8 * (lane & 7)));
+    }
+  }
+
+  auto issue = [&](int kt, auto par) {  // par: STG's register set, kt & 1
+    if constexpr (STG != 0) {
+      const int krem = (int)min<int64_t>(kend - kbeg - 64 * (int64_t)kt, 1 << 20);
+      da.template load<par>(Ab + (int64_t)kt * (AK ? 64 : 64 * g.lda), krem);
+      db.template load<par>(Bb + (int64_t)kt * (BKM ? 64 : 64 * g.ldb), krem);
+    } else {
+      const uint32_t st = lds0 + (uint32_t)((kt & 1) * STAGE);
+      da.issue(reinterpret_cast<const uint16_t*>(reinterpret_cast<const uint8_t*>(Ab) + kt * da.step), st, wave);
+      db.issue(reinterpret_cast<const uint16_t*>(reinterpret_cast<const uint8_t*>(Bb) + kt * db.step),
+               st + A_BYTES, wave);
+    }
+  };
+  auto put = [&](auto par) {  // STG: a loaded k tile (register set par) into stage par
+    if constexpr (STG != 0) {
+      da.template store<par>(smem + par * STAGE, wave, lane);
+      db.template store<par>(smem + par * STAGE + A_BYTES, wave, lane);
+    }
+  };
+  constexpr std::integral_constant<int, 0> I0{};
+  constexpr std::integral_constant<int, 1> I1{};
+  constexpr std::integral_constant<int, 2> I2{};
+  constexpr std::integral_constant<int, 3> I3{};
+  if constexpr (STG != 0) {
+    // no branch around a load (one would make the waits count the later
+    // loads too): past the last k tile it is loaded again and not used
+    issue(0, I0);
+    issue(min(1, nk - 1), I1);
+  } else {
+    issue(0, I0);
+    if (nk > 1) issue(1, I0);
+  }
+
   FragReader<BM, AK, TM> fa;
   FragReader<BN, BKM, TN> fb;
   fa.init(wm0, lane);
   fb.init(wn0, lane);
-
   f32x16 acc[TM][TN];
   static_for<TM>([&](auto i) {
     static_for<TN>([&](auto j) {
@@ -675,108 +694,82 @@ void gemm_dma_kernel(GemmArgs g) {
 #pragma unroll
   for (int i = 0; i < TM; ++i) dbs[i] = 0.0f;
 
-  // A whole tile's GELU' or residual operand is loaded into registers before
-  // the first copies (the oldest loads, so the first tile's wait covers
-  // them): the epilogue then starts without a memory round trip.
-  constexpr bool kPF = !STG && E != EPI_GENERIC && (E & (EPI_DACT | EPI_RESID)) != 0;
-  const bool whole = (STG || E != EPI_GENERIC) && g.full_epi && m0 + BM <= g.M && n0 + BN <= g.N;
-  u32x4 pf[kPF ? 4 * TM : 1];
-  if constexpr (kPF) {
-    if (whole) {
-      const int64_t ldp = (E & EPI_DACT) ? g.ldc : g.ldr;
-      const uint16_t* src = ((E & EPI_DACT) ? g.dact : g.resid) + ((m0 + wm0) * ldp + n0 + wn0);
-#pragma unroll
-      for (int t = 0; t < 4 * TM; ++t)
-        pf[t] = *reinterpret_cast<const u32x4*>(src + (uint32_t)(((lane >> 3) + 8 * t) * ldp + 8 * (lane & 7)));
-    }
-  }
-
-  auto issue = [&](int kt) {
-    if constexpr (STG) {
-      const int krem = (int)min<int64_t>(kend - kbeg - 64 * (int64_t)kt, 1 << 20);
-      da.load(64 * (int64_t)kt, krem);
-      db.load(64 * (int64_t)kt, krem);
-    } else {
-      const uint32_t st = lds0 + (uint32_t)((kt % S) * STAGE);
-      da.issue(reinterpret_cast<const uint16_t*>(reinterpret_cast<const uint8_t*>(Ab) + kt * da.step), st, wave);
-      db.issue(reinterpret_cast<const uint16_t*>(reinterpret_cast<const uint8_t*>(Bb) + kt * db.step),
-               st + A_BYTES, wave);
-    }
-  };
-  auto put = [&](int kt) {  // STG: the loaded k tile kt into its stage
-    if constexpr (STG) {
-      da.store(smem + (kt % S) * STAGE, wave, lane);
-      db.store(smem + (kt % S) * STAGE + A_BYTES, wave, lane);
-    }
-  };
-  if constexpr (STG) {
-    issue(0);
-    put(0);
-    if (nk > 1) issue(1);
+  if constexpr (STG != 0) {
+    put(I0);
+    issue(min(2, nk - 1), I0);
   } else {
-#pragma unroll
-    for (int s = 0; s < S - 1; ++s)
-      if (s < nk) issue(s);
+    if (nk > 1) wait_vmcnt<L>();
+    else wait_vmcnt<0>();
   }
+  __syncthreads();
 
-  for (int kt = 0; kt < nk; ++kt) {
+  // fragments double-buffered over the k steps of 16: the LDS reads of the
+  // next step are issued among the MFMAs of the current one
+  uint4 af[2][TM], bf[2][TN];
+  auto read = [&](auto set, auto kk, uint32_t sa) {
+    static_for<TM>([&](auto i) { af[set][i] = fa.template read<i, kk>(sa); });
+    static_for<TN>([&](auto j) { bf[set][j] = fb.template read<j, kk>(sa + A_BYTES); });
+  };
+  auto multiply = [&](auto set, bool db_now) {
+    static_for<TM>([&](auto i) {
+      static_for<TN>([&](auto j) { acc[i][j] = mfma32<DT>(bf[set][j], af[set][i], acc[i][j]); });
+    });
+    if constexpr (DBS) {
+      if (db_now) static_for<TM>([&](auto i) { dbs[i] += frag_sum8<DT>(af[set][i]); });
+    }
+    static_for<TM * TN>([&](auto x) {  // each MFMA with its share of the reads
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+      constexpr int n = (x + 1) * kReads / (TM * TN) - x * kReads / (TM * TN);
+      if constexpr (n > 0) __builtin_amdgcn_sched_group_barrier(0x100, n, 0);
+    });
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  read(I0, I0, lds0);
+  // one k tile; par = kt & 1 (STG only)
+  auto k_tile = [&](int kt, auto par) {
+    const uint32_t sa = lds0 + (uint32_t)((kt & 1) * STAGE);
+    const uint32_t sn = lds0 + (uint32_t)(((kt + 1) & 1) * STAGE);
     const bool db_now = dbw && kt == db_next;
     if (db_now) db_next += db_cols;
-    if constexpr (STG) {
-      __syncthreads();  // tile kt is in its stage, the other stage has been read
-      if (kt + 1 < nk) put(kt + 1);
-      if (kt + 2 < nk) issue(kt + 2);
-    } else {
-      // tile kt has landed once at most min(S - 2, nk - 1 - kt) later tiles are in flight
-      const int later = min(S - 2, nk - 1 - kt);
-      static_for<S - 1>([&](auto p) {
-        if (later == p) wait_vmcnt<p * L>();
-      });
-      __syncthreads();
-      if (kt + S - 1 < nk) issue(kt + S - 1);
+    if constexpr (STG != 0) {
+      // the other stage was read before the last barrier
+      constexpr std::integral_constant<int, 1 - par> other{};
+      if (kt + 1 < nk) put(other);
+      issue(min(kt + 3, nk - 1), other);
     }
-    const uint32_t sa = lds0 + (uint32_t)((kt % S) * STAGE), sb = sa + A_BYTES;
-    // fragments double-buffered over the four k steps of 16: the LDS reads
-    // of step kk + 1 are issued ahead of the MFMAs of step kk.  Products
-    // with an mn-major operand (dX, dW: transposing reads, two per
-    // fragment) interleave one MFMA with its share of those reads
-    // (scheduling group barriers: dW +8-17% on the ViT-B layers); the
-    // forward products (both operands k-major) issue the step's reads as a
-    // group before its MFMAs (scheduling barriers), which measured 1-2%
-    // faster for them.
-    constexpr bool kInterleave = !(AK && BKM);
-    uint4 af[2][TM], bf[2][TN];
-    static_for<TM>([&](auto i) { af[0][i] = fa.template read<i, 0>(sa); });
-    static_for<TN>([&](auto j) { bf[0][j] = fb.template read<j, 0>(sb); });
-    static_for<4>([&](auto kk) {
-      constexpr int cur = kk & 1, nxt = cur ^ 1;
-      if constexpr (kk + 1 < 4) {
-        static_for<TM>([&](auto i) { af[nxt][i] = fa.template read<i, kk + 1>(sa); });
-        static_for<TN>([&](auto j) { bf[nxt][j] = fb.template read<j, kk + 1>(sb); });
+    read(I1, I1, sa);
+    multiply(I0, db_now);
+    read(I0, I2, sa);
+    multiply(I1, db_now);
+    read(I1, I3, sa);
+    multiply(I0, db_now);
+    if (kt + 1 < nk) {
+      if constexpr (STG == 0) wait_vmcnt<0>();  // k tile kt + 1 has landed
+      __syncthreads();
+      if constexpr (STG == 0) {
+        if (kt + 2 < nk) issue(kt + 2, I0);
       }
-      if constexpr (!kInterleave) __builtin_amdgcn_sched_barrier(0);
-      static_for<TM>([&](auto i) {
-        static_for<TN>([&](auto j) { acc[i][j] = mfma32<DT>(bf[cur][j], af[cur][i], acc[i][j]); });
-      });
-      if constexpr (DBS) {
-        if (db_now) static_for<TM>([&](auto i) { dbs[i] += frag_sum8<DT>(af[cur][i]); });
-      }
-      if constexpr (!kInterleave) {
-        __builtin_amdgcn_sched_barrier(0);
-      } else if constexpr (kk + 1 < 4) {
-        static_for<TM * TN>([&](auto) {
-          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);              // one MFMA
-          __builtin_amdgcn_sched_group_barrier(0x100, kReadsPerMfma, 0);  // its LDS reads
-        });
-      }
-    });
+      read(I0, I0, sn);
+    }
+    multiply(I1, db_now);
+  };
+  if constexpr (STG != 0) {
+    int kt = 0;
+    for (; kt + 1 < nk; kt += 2) {
+      k_tile(kt, I0);
+      k_tile(kt + 1, I1);
+    }
+    if (kt < nk) k_tile(kt, I0);
+  } else {
+    for (int kt = 0; kt < nk; ++kt) k_tile(kt, I0);
   }
+
   if constexpr (DBS) {
     if (dbw) {
       int bad = 0;
       static_for<TM>([&](auto i) {
         const float other = __shfl_xor(dbs[i], 32);  // the row's other 8 k of every step
-        const int64_t row = m0 + wm0 + 32 * i + lane;
+        const int64_t row = mw + 32 * i + lane;
         if (lane < 32 && row < g.M) {
           const float v = dbs[i] + other;
           if (g.splits > 1) {
@@ -792,132 +785,22 @@ void gemm_dma_kernel(GemmArgs g) {
     }
   }
   // the accumulators hold C^T blocks (the MFMA operands are swapped above)
-  if constexpr (STG) {
-    if (g.splits == 1) {
-      __syncthreads();  // every wave is done reading the stage buffers
-      uint16_t* lds = reinterpret_cast<uint16_t*>(smem) + wave * (WM * (WN + 4));
-      if (whole)
-        gemm_epilogue_lds<DT, TM, TN, E>(g, acc, m0 + wm0, n0 + wn0, lane, offC, lds);
-      else
-        gemm_epilogue_lds<DT, TM, TN, E, true>(g, acc, m0 + wm0, n0 + wn0, lane, offC, lds, nullptr,
-                                               (int)min<int64_t>(WM, g.M - m0 - wm0),
-                                               (int)min<int64_t>(WN, g.N - n0 - wn0));
-      return;
-    }
-  } else if constexpr (E != EPI_GENERIC) {
-    if (whole) {  // uniform over the workgroup
-      __syncthreads();  // every wave is done reading the stage buffers
-      gemm_epilogue_lds<DT, TM, TN, E>(g, acc, m0 + wm0, n0 + wn0, lane, offC,
-                                       reinterpret_cast<uint16_t*>(smem) + wave * (WM * 68),
-                                       kPF ? pf : nullptr);
-      return;
-    }
+  if (g.splits > 1) {
+    gemm_partials<TM, TN>(g, acc, mw, nw, lane, split);
+    return;
   }
-  gemm_epilogue<DT, TM, TN, true>(g, acc, m0 + wm0, n0 + wn0, lane, split, offC);
-}
-
-// Persistent form of the direct-to-LDS kernel for one product without
-// split-K or batching: a grid of (workgroups per CU) x 256 workgroups walks
-// the tiles in strides of the grid, so every workgroup stays on one XCD and
-// its tiles keep the XCD-contiguous order of tile_origin.  Between two tiles
-// the next tile's first k tile is copied into stage 0 while the current
-// tile's epilogue stages its output through the LDS above stage 0, so the
-// copy's latency overlaps the epilogue instead of opening the next tile.
-template <int DT, int BM, int BN, int WM, int WN, int OCC, bool AK, bool BKM, int E>
-__global__ __launch_bounds__((BM / WM) * (BN / WN) * 64)
-__attribute__((amdgpu_waves_per_eu(OCC, OCC)))
-void gemm_dma_persistent_kernel(GemmArgs g) {
-  constexpr int NWAVES = (BM / WM) * (BN / WN);
-  constexpr int TM = WM / 32, TN = WN / 32;
-  constexpr int A_BYTES = BM * 64 * 2, B_BYTES = BN * 64 * 2;
-  constexpr int STAGE = A_BYTES + B_BYTES;
-  constexpr int EPI = NWAVES * WM * 68 * 2;  // epilogue staging, from the start of stage 1
-  constexpr int SMEM = STAGE + (STAGE > EPI ? STAGE : EPI);
-  __shared__ __attribute__((aligned(1024))) uint8_t smem[SMEM];
-  const uint32_t lds0 = lds_u32(smem);
-
-  const int tid = threadIdx.x;
-  const int lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wm0 = (wave / (BN / WN)) * WM;
-  const int wn0 = (wave % (BN / WN)) * WN;
-  const uint32_t ntiles = (uint32_t)(((g.M + BM - 1) / BM) * ((g.N + BN - 1) / BN));
-  const int nk = (int)(g.K / 64);
-
-  FragReader<BM, AK, TM> fa;
-  FragReader<BN, BKM, TN> fb;
-  fa.init(wm0, lane);
-  fb.init(wn0, lane);
-  DmaOperand<BM, AK, NWAVES> da;
-  DmaOperand<BN, BKM, NWAVES> db;
-  int64_t m0, n0;
-  const uint16_t* Ab;
-  const uint16_t* Bb;
-  auto setup = [&](uint32_t t) {
-    tile_origin_of<BM, BN>(t, ntiles, g.M, g.N, m0, n0);
-    Ab = g.A + (AK ? m0 * g.lda : m0);
-    Bb = g.B + (BKM ? n0 * g.ldb : n0);
-    da.init(g.lda, (int)min<int64_t>(BM, g.M - m0), wave, lane);
-    db.init(g.ldb, (int)min<int64_t>(BN, g.N - n0), wave, lane);
-  };
-  auto issue = [&](int kt) {
-    const uint32_t st = lds0 + (uint32_t)((kt & 1) * STAGE);
-    da.issue(reinterpret_cast<const uint16_t*>(reinterpret_cast<const uint8_t*>(Ab) + kt * da.step), st, wave);
-    db.issue(reinterpret_cast<const uint16_t*>(reinterpret_cast<const uint8_t*>(Bb) + kt * db.step),
-             st + A_BYTES, wave);
-  };
-
-  uint32_t t = blockIdx.x;
-  if (t >= ntiles) return;  // uniform over the workgroup
-  setup(t);
-  issue(0);
-  for (;;) {
-    f32x16 acc[TM][TN];
-    static_for<TM>([&](auto i) {
-      static_for<TN>([&](auto j) {
-#pragma unroll
-        for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.0f;
-      });
-    });
-    for (int kt = 0; kt < nk; ++kt) {
-      wait_vmcnt<0>();  // k tile kt (and everything issued before it) has landed
-      __syncthreads();
-      if (kt + 1 < nk) issue(kt + 1);
-      const uint32_t sa = lds0 + (uint32_t)((kt & 1) * STAGE), sb = sa + A_BYTES;
-      uint4 af[2][TM], bf[2][TN];
-      static_for<TM>([&](auto i) { af[0][i] = fa.template read<i, 0>(sa); });
-      static_for<TN>([&](auto j) { bf[0][j] = fb.template read<j, 0>(sb); });
-      static_for<4>([&](auto kk) {
-        constexpr int cur = kk & 1, nxt = cur ^ 1;
-        if constexpr (kk + 1 < 4) {
-          static_for<TM>([&](auto i) { af[nxt][i] = fa.template read<i, kk + 1>(sa); });
-          static_for<TN>([&](auto j) { bf[nxt][j] = fb.template read<j, kk + 1>(sb); });
-        }
-        __builtin_amdgcn_sched_barrier(0);
-        static_for<TM>([&](auto i) {
-          static_for<TN>([&](auto j) { acc[i][j] = mfma32<DT>(bf[cur][j], af[cur][i], acc[i][j]); });
-        });
-        __builtin_amdgcn_sched_barrier(0);
-      });
-    }
-    const int64_t me = m0, ne = n0;
-    const uint32_t tn = t + gridDim.x;
-    __syncthreads();  // every wave is done reading the stage buffers
-    if (tn < ntiles) {
-      setup(tn);
-      issue(0);  // lands in stage 0 while this tile's epilogue runs above it
-    }
-    if (E != EPI_GENERIC && g.full_epi && me + BM <= g.M && ne + BN <= g.N) {
-      if constexpr (E != EPI_GENERIC)
-        gemm_epilogue_lds<DT, TM, TN, E>(g, acc, me + wm0, ne + wn0, lane, 0,
-                                         reinterpret_cast<uint16_t*>(smem + STAGE) + wave * (WM * 68));
-    } else {
-      gemm_epilogue<DT, TM, TN, true>(g, acc, me + wm0, ne + wn0, lane, 0, 0);
-    }
-    if (tn >= ntiles) break;
-    t = tn;
-    __syncthreads();  // the epilogue's LDS (stage 1) is free for the next copies
-  }
+  __syncthreads();  // every wave is done reading the stage buffers
+  uint16_t* lds = reinterpret_cast<uint16_t*>(smem) + wave * (WM * (EC + 4));
+  static_for<(TN + 1) / 2>([&](auto c) {
+    constexpr int J0 = 2 * c, TC = TN - J0 < 2 ? TN - J0 : 2;
+    if (whole)
+      gemm_epilogue_lds<DT, TM, TC, E, false, J0>(g, acc, mw, nw + 32 * J0, lane, offC, lds,
+                                                  kPF ? pf : nullptr);
+    else
+      gemm_epilogue_lds<DT, TM, TC, E, true, J0>(g, acc, mw, nw + 32 * J0, lane, offC, lds, nullptr,
+                                                 (int)min<int64_t>(WM, g.M - mw),
+                                                 (int)min<int64_t>(32 * TC, g.N - nw - 32 * J0));
+  });
 }
 
 // Sum of split-K partials in split order, one rounding: C = half(sum_s W[s]),
@@ -1019,180 +902,113 @@ static bool full_epilogue_ok(const GemmArgs& g, int bm) {
          g.ldr * bm < ((int64_t)1 << 30);
 }
 
-template <int DT, int BM, int BN, int WM, int WN, int S, int OCC>
-hipError_t launch_dma(GemmArgs g, bool ak, bool bk, int64_t nbatch, hipStream_t s) {
+// Direct-to-LDS tiles.  The 128 x 128 ones take every layout; the others a
+// k-major A (forward, dX) without split-K.
+template <int DT, int BM, int BN, int WM, int WN, int OCC>
+hipError_t launch_tiles(GemmArgs g, bool ak, bool bk, int64_t nbatch, hipStream_t s) {
   constexpr int NT = (BM / WM) * (BN / WN) * 64;
   const int64_t tiles = ((g.M + BM - 1) / BM) * ((g.N + BN - 1) / BN);
   dim3 grid((unsigned)tiles, (unsigned)(g.splits > 1 ? g.splits : nbatch));
   g.full_epi = full_epilogue_ok(g, BM) ? 1 : 0;
-  // a call that counts non-finite outputs (weight gradients: both operands
-  // mn-major, no epilogue operation) has a whole-tile variant of its own;
-  // any other counting call takes the generic epilogue
-  const int e = g.full_epi ? epilogue_mask(g) | (g.nonfinite ? EPI_COUNT : 0) : EPI_GENERIC;
-#define MPX_D(AKv, BKv, Ev) gemm_dma_kernel<DT, BM, BN, WM, WN, S, OCC, AKv, BKv, Ev><<<grid, NT, 0, s>>>(g)
-#define MPX_DB(Ev) gemm_dma_kernel<DT, BM, BN, WM, WN, S, OCC, false, false, Ev, true><<<grid, NT, 0, s>>>(g)
-  if constexpr (BM == 64) {
-    // 64 x 128 tiles (outputs too small to fill the CUs with 128 x 128): the
-    // A operand must be k-major (dma_ok rejects the rest)
-    if (!ak) return hipErrorInvalidValue;
-    if (bk) {
-      switch (e) {
-        case 0: MPX_D(true, true, 0); break;
-        case EPI_BIAS: MPX_D(true, true, EPI_BIAS); break;
-        case EPI_BIAS | EPI_GELU: MPX_D(true, true, EPI_BIAS | EPI_GELU); break;
-        case EPI_BIAS | EPI_RESID: MPX_D(true, true, EPI_BIAS | EPI_RESID); break;
-        default: MPX_D(true, true, EPI_GENERIC);
-      }
-    } else {
-      switch (e) {
-        case 0: MPX_D(true, false, 0); break;
-        case EPI_DACT: MPX_D(true, false, EPI_DACT); break;
-        default: MPX_D(true, false, EPI_GENERIC);
-      }
+  const int e = epilogue_mask(g) | (g.nonfinite ? EPI_COUNT : 0);
+#define MPX_T(AKv, BKv, Ev, DBv) \
+  gemm_tile_kernel<DT, BM, BN, WM, WN, OCC, AKv, BKv, Ev, DBv><<<grid, NT, 0, s>>>(g)
+  if (ak && bk) {
+    switch (e) {
+      case EPI_BIAS: MPX_T(true, true, EPI_BIAS, false); break;
+      case EPI_BIAS | EPI_GELU: MPX_T(true, true, EPI_BIAS | EPI_GELU, false); break;
+      case EPI_BIAS | EPI_RESID: MPX_T(true, true, EPI_BIAS | EPI_RESID, false); break;
+      default: MPX_T(true, true, EPI_GENERIC, false);
     }
-  } else if constexpr (BM == 128 && BN == 128 && S == 2) {
-    // the configuration the dispatcher picks: whole tiles get the
-    // specialised epilogue of each call pattern of the training step
-    if (ak && bk) {
-      switch (e) {
-        case 0: MPX_D(true, true, 0); break;
-        case EPI_BIAS: MPX_D(true, true, EPI_BIAS); break;
-        case EPI_BIAS | EPI_GELU: MPX_D(true, true, EPI_BIAS | EPI_GELU); break;
-        case EPI_BIAS | EPI_RESID: MPX_D(true, true, EPI_BIAS | EPI_RESID); break;
-        default: MPX_D(true, true, EPI_GENERIC);
-      }
-    } else if (ak && !bk) {
-      switch (e) {
-        case 0: MPX_D(true, false, 0); break;
-        case EPI_DACT: MPX_D(true, false, EPI_DACT); break;
-        default: MPX_D(true, false, EPI_GENERIC);
-      }
-    } else if (!ak && bk) {
-      if (e == 0) MPX_D(false, true, 0);
-      else MPX_D(false, true, EPI_GENERIC);
+  } else if (ak) {
+    switch (e) {
+      case 0: MPX_T(true, false, 0, false); break;
+      case EPI_DACT: MPX_T(true, false, EPI_DACT, false); break;
+      default: MPX_T(true, false, EPI_GENERIC, false);
+    }
+  } else if constexpr (BM == 128 && BN == 128) {
+    if (bk) {
+      MPX_T(false, true, EPI_GENERIC, false);
     } else if (g.db) {  // weight gradient with the bias gradient summed alongside
-      if (e == 0) MPX_DB(0);
-      else if (e == EPI_COUNT) MPX_DB(EPI_COUNT);
-      else MPX_DB(EPI_GENERIC);
+      MPX_T(false, false, EPI_GENERIC, true);
     } else {
-      if (e == 0) MPX_D(false, false, 0);
-      else if (e == EPI_COUNT) MPX_D(false, false, EPI_COUNT);
-      else MPX_D(false, false, EPI_GENERIC);
+      MPX_T(false, false, EPI_GENERIC, false);
     }
   } else {
-    if (ak && bk) MPX_D(true, true, EPI_GENERIC);
-    else if (ak && !bk) MPX_D(true, false, EPI_GENERIC);
-    else if (!ak && bk) MPX_D(false, true, EPI_GENERIC);
-    else MPX_D(false, false, EPI_GENERIC);
+    return hipErrorInvalidValue;
   }
-#undef MPX_D
-#undef MPX_DB
+#undef MPX_T
   return hipGetLastError();
 }
 
-// Operands staged through registers: any alignment, any reduction length.
+// Operands only StagedOperand's ANY form takes: rows of fewer than 8 values (no
+// 16-byte load fits) or lane offsets past 31 bits.
+inline bool staged_any(const GemmArgs& g, bool ak, bool bk) {
+  const int64_t lim = ((int64_t)1 << 31) - 4096;
+  return (ak ? g.K : g.M) < 8 || (bk ? g.K : g.N) < 8 || g.lda * 256 >= lim || g.ldb * 256 >= lim;
+}
+
+// Operands staged through registers: any alignment, any reduction length
+// (128 x 128 tiles: not for operands of staged_any).
 template <int DT, int BM, int BN, int WM, int WN>
 hipError_t launch_staged(GemmArgs g, bool ak, bool bk, int64_t nbatch, hipStream_t s) {
   constexpr int NT = (BM / WM) * (BN / WN) * 64;
   const int64_t tiles = ((g.M + BM - 1) / BM) * ((g.N + BN - 1) / BN);
   dim3 grid((unsigned)tiles, (unsigned)(g.splits > 1 ? g.splits : nbatch));
   g.full_epi = full_epilogue_ok(g, BM) ? 1 : 0;
-#define MPX_S(AKv, BKv, Ev, DBv) \
-  gemm_dma_kernel<DT, BM, BN, WM, WN, 2, 2, AKv, BKv, Ev, DBv, true><<<grid, NT, 0, s>>>(g)
-  if constexpr (BM == 128) {  // the training step's epilogues compiled in
-    const int e = epilogue_mask(g) | (g.nonfinite ? EPI_COUNT : 0);
-    if (ak && bk) {
-      switch (e) {
-        case EPI_BIAS: MPX_S(true, true, EPI_BIAS, false); break;
-        case EPI_BIAS | EPI_GELU: MPX_S(true, true, EPI_BIAS | EPI_GELU, false); break;
-        default: MPX_S(true, true, EPI_GENERIC, false);
-      }
-    } else if (ak) {
-      if (e == 0) MPX_S(true, false, 0, false);
-      else MPX_S(true, false, EPI_GENERIC, false);
-    } else if (bk) {
-      MPX_S(false, true, EPI_GENERIC, false);
-    } else if (g.db) {
-      MPX_S(false, false, EPI_GENERIC, true);
-    } else {
-      MPX_S(false, false, EPI_GENERIC, false);
-    }
+#define MPX_S(AKv, BKv, Ev, DBv, STGv) \
+  gemm_tile_kernel<DT, BM, BN, WM, WN, 2, AKv, BKv, Ev, DBv, STGv><<<grid, NT, 0, s>>>(g)
+#define MPX_S_LAYOUTS(STGv)                                       \
+  do {                                                            \
+    if (ak && bk) MPX_S(true, true, EPI_GENERIC, false, STGv);    \
+    else if (ak) MPX_S(true, false, EPI_GENERIC, false, STGv);    \
+    else if (bk) MPX_S(false, true, EPI_GENERIC, false, STGv);    \
+    else if (g.db) MPX_S(false, false, EPI_GENERIC, true, STGv);  \
+    else MPX_S(false, false, EPI_GENERIC, false, STGv);           \
+  } while (0)
+  if constexpr (BM == 128) {  // the forward's epilogues compiled in
+    const int e = epilogue_mask(g);
+    if (ak && bk && e == EPI_BIAS) MPX_S(true, true, EPI_BIAS, false, 1);
+    else if (ak && bk && e == (EPI_BIAS | EPI_GELU)) MPX_S(true, true, EPI_BIAS | EPI_GELU, false, 1);
+    else MPX_S_LAYOUTS(1);
+  } else if (staged_any(g, ak, bk)) {
+    MPX_S_LAYOUTS(2);
   } else {
-    if (ak && bk) MPX_S(true, true, EPI_GENERIC, false);
-    else if (ak) MPX_S(true, false, EPI_GENERIC, false);
-    else if (bk) MPX_S(false, true, EPI_GENERIC, false);
-    else if (g.db) MPX_S(false, false, EPI_GENERIC, true);
-    else MPX_S(false, false, EPI_GENERIC, false);
+    MPX_S_LAYOUTS(1);
   }
+#undef MPX_S_LAYOUTS
 #undef MPX_S
   return hipGetLastError();
 }
 
-template <int DT, int BM, int BN, int WM, int WN, int OCC>
-hipError_t launch_persistent(GemmArgs g, bool ak, bool bk, hipStream_t s) {
-  constexpr int NT = (BM / WM) * (BN / WN) * 64;
-  const int64_t tiles = ((g.M + BM - 1) / BM) * ((g.N + BN - 1) / BN);
-  const unsigned grid = (unsigned)std::min<int64_t>(tiles, 256 * OCC);
-  g.full_epi = full_epilogue_ok(g, BM) ? 1 : 0;
-  // a call that counts non-finite outputs takes the generic epilogue
-  const int e = g.full_epi && !g.nonfinite ? epilogue_mask(g) : EPI_GENERIC;
-  if (!ak) return hipErrorInvalidValue;
-#define MPX_P(BKv, Ev) gemm_dma_persistent_kernel<DT, BM, BN, WM, WN, OCC, true, BKv, Ev><<<grid, NT, 0, s>>>(g)
-  if (bk) {
-    switch (e) {
-      case 0: MPX_P(true, 0); break;
-      case EPI_BIAS: MPX_P(true, EPI_BIAS); break;
-      case EPI_BIAS | EPI_GELU: MPX_P(true, EPI_BIAS | EPI_GELU); break;
-      case EPI_BIAS | EPI_RESID: MPX_P(true, EPI_BIAS | EPI_RESID); break;
-      default: MPX_P(true, EPI_GENERIC);
-    }
-  } else {
-    switch (e) {
-      case 0: MPX_P(false, 0); break;
-      case EPI_DACT: MPX_P(false, EPI_DACT); break;
-      default: MPX_P(false, EPI_GENERIC);
-    }
-  }
-#undef MPX_P
-  return hipGetLastError();
-}
-
 // The launchers are compiled in three sources per half type, which build in
-// parallel: the configurations the dispatcher picks (gemm_f16.hip), the
-// register-staged ones (gemm_staged_f16.hip) and the ones only forced
-// (gemm_forced_f16.hip); likewise for bf16.
+// parallel: the 128 x 128 and 64 x 128 tiles (gemm_f16.hip), the wide ones
+// (gemm_wide_f16.hip) and the register-staged ones (gemm_staged_f16.hip);
+// likewise for bf16.
 #define MPX_GEMM_STAGED(X, DT)                                                              \
   X template hipError_t launch_staged<DT, 64, 64, 32, 32>(GemmArgs, bool, bool, int64_t, hipStream_t); \
   X template hipError_t launch_staged<DT, 128, 128, 64, 64>(GemmArgs, bool, bool, int64_t, hipStream_t);
-#define MPX_GEMM_FORCED(X, DT)                                                              \
-  X template hipError_t launch_dma<DT, 256, 256, 128, 128, 2, 1>(GemmArgs, bool, bool, int64_t, hipStream_t); \
-  X template hipError_t launch_dma<DT, 256, 128, 128, 64, 3, 1>(GemmArgs, bool, bool, int64_t, hipStream_t); \
-  X template hipError_t launch_dma<DT, 128, 256, 64, 128, 3, 1>(GemmArgs, bool, bool, int64_t, hipStream_t); \
-  X template hipError_t launch_dma<DT, 128, 128, 64, 64, 4, 1>(GemmArgs, bool, bool, int64_t, hipStream_t); \
-  X template hipError_t launch_persistent<DT, 128, 128, 64, 64, 2>(GemmArgs, bool, bool, hipStream_t); \
-  X template hipError_t launch_persistent<DT, 64, 128, 32, 64, 3>(GemmArgs, bool, bool, hipStream_t);
+#define MPX_GEMM_WIDE(X, DT)                                                                \
+  X template hipError_t launch_tiles<DT, 256, 256, 128, 64, 2>(GemmArgs, bool, bool, int64_t, hipStream_t); \
+  X template hipError_t launch_tiles<DT, 128, 192, 64, 96, 2>(GemmArgs, bool, bool, int64_t, hipStream_t);
 #ifndef MPX_GEMM_STAGED_SOURCE
 MPX_GEMM_STAGED(extern, MPX_F16)
 MPX_GEMM_STAGED(extern, MPX_BF16)
 #endif
-#ifndef MPX_GEMM_FORCED_SOURCE
-MPX_GEMM_FORCED(extern, MPX_F16)
-MPX_GEMM_FORCED(extern, MPX_BF16)
+#ifndef MPX_GEMM_WIDE_SOURCE
+MPX_GEMM_WIDE(extern, MPX_F16)
+MPX_GEMM_WIDE(extern, MPX_BF16)
 #endif
 
 // Tile configurations (the value of mpx_gemm_set_config):
 //   1  register-staged 64 x 64, 4 waves of 32 x 32    (any operands)
 //   2  register-staged 128 x 128, 4 waves of 64 x 64  (any operands)
-//   3  direct-to-LDS 256 x 256, 4 waves, 2 stages
-//   4  direct-to-LDS 256 x 128, 4 waves, 3 stages
-//   5  direct-to-LDS 128 x 256, 4 waves, 3 stages
-//   6  direct-to-LDS 128 x 128, 4 waves, 4 stages
-//   7  direct-to-LDS 128 x 128, 4 waves, 2 stages, two workgroups per CU
+// direct-to-LDS:
+//   3  256 x 256, 8 waves of 128 x 64, one workgroup per CU    (A k-major)
+//   5  128 x 192, 4 waves of 64 x 96, two workgroups per CU    (A k-major; also 4)
+//   7  128 x 128, 4 waves of 64 x 64, two workgroups per CU    (also 6, 10)
+//   9  64 x 128, 4 waves of 32 x 64, three workgroups per CU   (A k-major; also 11)
 //   8  skinny products: one wave (K > 32) or one lane (K <= 32) per output
-//   9  direct-to-LDS 64 x 128, 4 waves of 32 x 64, 2 stages, three workgroups
-//      per CU (A k-major only)
-//  10  configuration 7, persistent (A k-major, no split-K or batch)
-//  11  configuration 9, persistent (A k-major, no split-K or batch)
 extern int g_forced_config;  // defined in gemm.hip
 
 // The direct-to-LDS kernel needs 16-byte aligned operands and whole k tiles
@@ -1205,46 +1021,63 @@ static bool dma_ok(const GemmArgs& g, bool vec, bool ak, bool bk) {
   return spanA < lim && spanB < lim;
 }
 
-// Measured on MI355X over the transformer layer shapes (M 8320..25216, N and K
-// 384..3072) and 8192^3: configuration 7 (two co-resident workgroups hide
-// each other's epilogue and pipeline bubbles) is the fastest direct-to-LDS
-// variant at full occupancy, forward and backward; the register-staged
-// kernels serve operands the copies cannot take.  What remains is tile
-// quantisation: 128 x 128 tiles run 512 at a time (2 per CU), 64 x 128
-// tiles 768 at a time (3 per CU) with half the work each, so an output
-// whose 128 x 128 tile count sits just above a multiple of 512 runs a
-// nearly empty last round.  Cost of a configuration = rounds x
-// (workgroups per CU) x (tile area), with 5% added for the smaller tiles'
-// lower MFMA efficiency; the 64 x 128 tiles are taken when they save more
-// than 3% (on the ViT layer shapes this picks the faster of the two in
-// every measured case, e.g. 12608 x 768 outputs: 22 us instead of 29).
 static bool small_ok(const GemmArgs& g, int64_t nbatch);
 
-static bool prefer_64x128(const GemmArgs& g, int64_t nbatch) {
-  const int64_t nb = g.splits > 1 ? g.splits : nbatch;
-  const int64_t tn = (g.N + 127) / 128;
-  const int64_t t128 = ((g.M + 127) / 128) * tn * nb, t64 = ((g.M + 63) / 64) * tn * nb;
-  const double cost128 = (double)((t128 + 511) / 512) * 2.0 * 2.0;
-  const double cost64 = (double)((t64 + 767) / 768) * 3.0 * 1.05;
-  return cost64 < 0.97 * cost128;
+// Direct-to-LDS tiles for a k-major A, by estimated time.  A chip of 256 CUs
+// runs 256 x per_cu tiles at a time; a round of o tiles per CU takes
+// nk x k_us[o - 1] (nk k tiles of 64) plus o x tile_us for what surrounds the
+// k loops (tile_us[1]: epilogues that read or write a second matrix), and the
+// last round has only as many tiles per CU as are left.  The constants are
+// fitted to 280 measured products with operands from HBM (M 128..25216, N and
+// K 128..3072; forward with bias, GELU or residual, dX, dX through GELU'):
+// the choice is on average 0.5% slower than the fastest, 64 x 128 alone 6%,
+// 128 x 128 alone 10%.  256 x 256 is charged 10% more than its fit: between
+// other products it loses that (the MLP of a 384-wide block, whole: 240 us
+// with it, 234 with 128 x 128, which alone are within 2%).  Examples (us;
+// 256 x 256, 128 x 192, 128 x 128, 64 x 128): 12608 x 2304 x 768 dX
+// 49 / 51 / 51 / 58; 12608 x 768 x 3072 forward 78 / 66 / 80 / 87; 16640 x 384
+// x 1536 44 / 34 / 29 / 41; 8320 x 384 x 384 16.6 / 10.0 / 9.0 / 8.9.
+struct TileCost {
+  int config, bm, bn, per_cu;
+  double k_us[3], tile_us[2];
+};
+static int choose_tiles(const GemmArgs& g, int64_t nbatch) {
+  static const TileCost costs[] = {
+      {9, 64, 128, 3, {0.35, 0.56, 0.94}, {0.73, 1.26}},
+      {7, 128, 128, 2, {0.62, 0.60, 0}, {2.37, 2.76}},
+      {5, 128, 192, 2, {0.85, 0.83, 0}, {2.06, 4.35}},
+      {3, 256, 256, 1, {1.20, 0, 0}, {7.2, 13.0}},
+  };
+  const int second = g.pre || g.dact || g.resid ? 1 : 0;
+  const double nk = (double)(g.K / 64);
+  int best = 7;
+  double least = 0.0;
+  for (const TileCost& c : costs) {
+    const int64_t tiles = ((g.M + c.bm - 1) / c.bm) * ((g.N + c.bn - 1) / c.bn) * nbatch;
+    auto round = [&](int64_t o) { return o ? nk * c.k_us[o - 1] + c.tile_us[second] * (double)o : 0.0; };
+    const double t = (double)(tiles / (256 * c.per_cu)) * round(c.per_cu) +
+                     round((tiles % (256 * c.per_cu) + 255) / 256);
+    if (least == 0.0 || t < least) {
+      least = t;
+      best = c.config;
+    }
+  }
+  return best;
 }
 
 static int choose_config(const GemmArgs& g, bool vec, bool ak, bool bk, int64_t nbatch) {
   const bool dma = dma_ok(g, vec, ak, bk);
   const bool small = small_ok(g, nbatch);
-  const int f = g_forced_config;
+  int f = g_forced_config;
+  f = f == 4 ? 5 : f == 6 || f == 10 ? 7 : f == 11 ? 9 : f;
   if (f == 8 && small) return 8;
-  if (f == 9 && dma && ak) return 9;
-  if ((f == 10 || f == 11) && dma && ak) return g.splits == 1 && nbatch == 1 ? f : (f == 10 ? 7 : 9);
-  if (f >= 3 && f <= 7 && dma) return f;
-  if (f == 1 || f == 2) return f;
+  if (f == 7 && dma) return 7;
+  if ((f == 3 || f == 5 || f == 9) && dma && ak && g.splits == 1) return f;
+  const bool any = staged_any(g, ak, bk);
+  if (f == 1 || f == 2) return any ? 1 : f;
   if (small && (g.M <= 32 || g.N <= 32 || g.K <= 32)) return 8;
-  if (g.M <= 64 || g.N <= 64) return 1;
-  // (the persistent forms 10 and 11 are 1-5% faster on a product alone, but
-  // they hold every workgroup slot of the chip until they end, so the
-  // weight-gradient stream of the training step cannot interleave: the ViT
-  // steps ran 2-4% slower with them)
-  if (dma) return ak && prefer_64x128(g, nbatch) ? 9 : 7;
+  if (any || g.M <= 64 || g.N <= 64) return 1;
+  if (dma) return ak && g.splits == 1 ? choose_tiles(g, nbatch) : 7;
   return 2;
 }
 
@@ -1323,14 +1156,10 @@ static hipError_t run_gemm(GemmArgs g, bool ak, bool bk, int64_t nbatch, hipStre
     case 8: return launch_small<DT>(g, ak, bk, s);
     case 1: return launch_staged<DT, 64, 64, 32, 32>(g, ak, bk, nbatch, s);
     case 2: return launch_staged<DT, 128, 128, 64, 64>(g, ak, bk, nbatch, s);
-    case 3: return launch_dma<DT, 256, 256, 128, 128, 2, 1>(g, ak, bk, nbatch, s);
-    case 4: return launch_dma<DT, 256, 128, 128, 64, 3, 1>(g, ak, bk, nbatch, s);
-    case 5: return launch_dma<DT, 128, 256, 64, 128, 3, 1>(g, ak, bk, nbatch, s);
-    case 6: return launch_dma<DT, 128, 128, 64, 64, 4, 1>(g, ak, bk, nbatch, s);
-    case 7: return launch_dma<DT, 128, 128, 64, 64, 2, 2>(g, ak, bk, nbatch, s);
-    case 9: return launch_dma<DT, 64, 128, 32, 64, 2, 3>(g, ak, bk, nbatch, s);
-    case 10: return launch_persistent<DT, 128, 128, 64, 64, 2>(g, ak, bk, s);
-    case 11: return launch_persistent<DT, 64, 128, 32, 64, 3>(g, ak, bk, s);
+    case 3: return launch_tiles<DT, 256, 256, 128, 64, 2>(g, ak, bk, nbatch, s);
+    case 5: return launch_tiles<DT, 128, 192, 64, 96, 2>(g, ak, bk, nbatch, s);
+    case 7: return launch_tiles<DT, 128, 128, 64, 64, 2>(g, ak, bk, nbatch, s);
+    case 9: return launch_tiles<DT, 64, 128, 32, 64, 3>(g, ak, bk, nbatch, s);
     default: return hipErrorInvalidValue;
   }
 }
