@@ -169,6 +169,7 @@ static int linear_bwd(const char* fn, const void* X, const void* W, const void* 
   }
   hipStream_t s = (hipStream_t)stream;
   if (dt == MPX_F32) {  // full precision: the same three products in float32
+    bool db_fused32 = false;
     if (dX) {
       GemmF32Args g = f32_args();
       g.A = (const float*)dY;
@@ -186,6 +187,7 @@ static int linear_bwd(const char* fn, const void* X, const void* W, const void* 
       g.C = (float*)dW;
       g.M = N; g.N = K; g.K = M;
       g.lda = N; g.ldb = K; g.ldc = K;
+      g.db = (float*)db;
       int sp;
       int64_t ks;
       split_plan(N, K, M, sp, ks);
@@ -193,13 +195,15 @@ static int linear_bwd(const char* fn, const void* X, const void* W, const void* 
         g.splits = sp;
         g.k_split = ks;
         g.ws = (float*)workspace;
-        MPX_HIP(launch_gemm_f32(g, false, false, 1, s));
-        MPX_HIP(launch_splitk_reduce_f32(g.ws, sp, N * K, (float*)dW, s));
+        g.dbp = db ? (float*)((char*)workspace + db_partials_offset(sp, N, K)) : nullptr;
+        MPX_HIP(launch_gemm_f32(g, false, false, 1, s, &db_fused32));
+        MPX_HIP(launch_splitk_reduce_f32(g.ws, sp, N * K, (float*)dW, g.dbp, db_fused32 ? N : 0, (float*)db,
+                                         s));
       } else {
-        MPX_HIP(launch_gemm_f32(g, false, false, 1, s));
+        MPX_HIP(launch_gemm_f32(g, false, false, 1, s, &db_fused32));
       }
     }
-    if (db) MPX_HIP(launch_colsum_f32((const float*)dY, M, N, (float*)workspace, (float*)db, s));
+    if (db && !db_fused32) MPX_HIP(launch_colsum_f32((const float*)dY, M, N, (float*)workspace, (float*)db, s));
     return MPX_OK;
   }
   // dX[M,K] = dY[M,N] W[N,K]: A = dY (k-major over N), B(n=k', k=n) = W[n*K + k'] (mn-major)

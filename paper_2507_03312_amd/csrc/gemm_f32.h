@@ -31,11 +31,19 @@ struct GemmF32Args {
   const float* dact;
   int32_t act;
   int64_t sA0, sA1, sB0, sB1, sC0, sC1, nb1;
+  // if set (products with an mn-major A): db[m] = sum_k A(m, k) as well, or
+  // with split-K the partial sums dbp[split][M]
+  float* db;
+  float* dbp;
 };
 
-hipError_t launch_gemm_f32(const GemmF32Args& g, bool ak, bool bk, int64_t nbatch, hipStream_t s);
-// C[i] = sum over s < splits of ws[s*MN + i], in split order
-hipError_t launch_splitk_reduce_f32(const float* ws, int splits, int64_t MN, float* C, hipStream_t s);
+// db_fused (nullable) tells whether the chosen kernel summed g.db / g.dbp
+hipError_t launch_gemm_f32(GemmF32Args g, bool ak, bool bk, int64_t nbatch, hipStream_t s,
+                           bool* db_fused = nullptr);
+// C[i] = sum over s < splits of ws[s*MN + i], in split order, and db[m] =
+// sum over s of dbp[s*rows + m] likewise (rows 0: none)
+hipError_t launch_splitk_reduce_f32(const float* ws, int splits, int64_t MN, float* C, const float* dbp,
+                                    int64_t rows, float* db, hipStream_t s);
 // out[col] = sum over rows of X[r, col] (dense float32 X), float32 partials
 // over row slices in `ws` (colsum_workspace bytes), added in slice order
 hipError_t launch_colsum_f32(const float* X, int64_t rows, int64_t cols, float* ws, float* out,

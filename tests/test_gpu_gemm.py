@@ -525,6 +525,43 @@ def test_gemm_batched_f32(tr):
     assert_within(got, ref, bound, "batched f32")
 
 
+@pytest.mark.parametrize("tr", [(0, 1), (0, 0), (1, 0), (1, 1)], ids=str)
+@pytest.mark.parametrize("mnk", [(128, 128, 32), (132, 260, 64), (4, 136, 96), (300, 4, 1056)],
+                         ids=lambda s: "x".join(map(str, s)))
+def test_f32_direct_copies(tr, mnk):
+    """Float32 products on the direct-to-LDS kernel (16-byte rows, a reduction
+    that is a multiple of 32), every layout, on ragged tiles: operand rows are
+    padded with NaN and output rows with a mark."""
+    M, N, K = mnk
+    a, b = _rand32((M, K), 81), _rand32((N, K), 82)
+    pad = lambda m: torch.nn.functional.pad(_dev32(m), (0, 4), value=float("nan")).contiguous()  # noqa: E731
+    pa, pb = pad(a.T if tr[0] else a), pad(b if tr[1] else b.T)
+    pc = torch.full((M, N + 4), 7.0, device="cuda")
+    mx.mpx_gemm_batched(tr[0], tr[1], M, N, K, 1, 1, pa.data_ptr(), pa.shape[1], 0, 0, pb.data_ptr(), pb.shape[1],
+                        0, 0, pc.data_ptr(), N + 4, 0, 0, mx.MPX_F32, _s())
+    ref = a.astype(np.float64) @ b.astype(np.float64).T
+    got = to_host(pc)
+    assert_within(got[:, :N], ref, gemm_bound(a, b.T, ref, "f32", K), "C")
+    assert np.all(got[:, N:] == 7.0)
+
+
+@pytest.mark.parametrize("mnk", [(2112, 132, 260), (96, 260, 132), (2100, 132, 260)], ids=lambda s: "x".join(map(str, s)))
+def test_f32_bias_gradient(mnk):
+    """dW and db together: summed in the product's kernel (split-K and not),
+    and by the column sums where the rows do not allow it."""
+    M, N, K = mnk
+    x, dy = _rand32((M, K), 83), _rand32((M, N), 84)
+    tx, tdy, gdw, gdb = _dev32(x), _dev32(dy), _zeros32(N, K), _zeros32(N)
+    n = mx.mpx_linear_bwd_workspace(M, N, K)
+    ws = torch.zeros(n, dtype=torch.uint8, device="cuda")
+    mx.mpx_linear_bwd(tx.data_ptr(), None, tdy.data_ptr(), None, mx.MPX_ACT_NONE, None, gdw.data_ptr(),
+                      gdb.data_ptr(), M, N, K, mx.MPX_F32, ws.data_ptr(), n, None, _s())
+    ref = dy.astype(np.float64).T @ x.astype(np.float64)
+    assert_within(to_host(gdw), ref, gemm_bound(dy.T, x, ref, "f32", M), "dW")
+    rdb = dy.astype(np.float64).sum(0)
+    assert_within(to_host(gdb), rdb, ulp(rdb, "f32") + 2.0 * M * 2.0 ** -24 * np.abs(dy).sum(0), "db")
+
+
 @pytest.mark.parametrize("config", [0, 1, 2])
 @pytest.mark.parametrize("tr", [(0, 1), (0, 0), (1, 0), (1, 1)], ids=str)
 @pytest.mark.parametrize("mnk", [(65, 67, 9), (130, 129, 63), (129, 200, 65), (40, 136, 588), (64, 128, 5),
