@@ -81,6 +81,12 @@ struct RowStage {
   }
 };
 
+// exp(scale x) on the hardware exp2, c2 = scale log2(e): for differences x
+// of unscaled scores.  scale is a power of two (1/8), so (x) c2 rounds as
+// (scale x) log2(e) does, with one multiplication per score less in each pass.
+constexpr float kLog2e = 1.4426950408889634f;
+__device__ __forceinline__ float exp_scaled(float x, float c2) { return __builtin_amdgcn_exp2f(x * c2); }
+
 // Packs 4 halves.
 __device__ __forceinline__ u32x2 pack4(uint16_t a, uint16_t b, uint16_t c, uint16_t d) {
   return u32x2{a | ((uint32_t)b << 16), c | ((uint32_t)d << 16)};
@@ -179,6 +185,7 @@ __global__ __launch_bounds__(NB * 64) void attn_fwd_rows_kernel(const uint16_t* 
   });
 
   // softmax over the keys of query q (float32; S rounded to half first)
+  const float c2 = scale * kLog2e;
   // (blocks below nfull have no key past T: no masks there)
   const int nfull = T / 32;
   float mx = -INFINITY;
@@ -187,8 +194,8 @@ __global__ __launch_bounds__(NB * 64) void attn_fwd_rows_kernel(const uint16_t* 
     for (int e = 0; e < 16; e += 2) {
       float a, c;
       unpack2<DT>(pack2<DT>(s[j][e], s[j][e + 1]), a, c);
-      s[j][e] = a * scale;
-      s[j][e + 1] = c * scale;
+      s[j][e] = a;
+      s[j][e + 1] = c;
     }
     if (j >= nfull) {
 #pragma unroll
@@ -202,7 +209,7 @@ __global__ __launch_bounds__(NB * 64) void attn_fwd_rows_kernel(const uint16_t* 
   float sum = 0.0f;
   static_for<NB>([&](auto j) {
 #pragma unroll
-    for (int e = 0; e < 16; ++e) s[j][e] = __expf(s[j][e] - mx);
+    for (int e = 0; e < 16; ++e) s[j][e] = exp_scaled(s[j][e] - mx, c2);
     if (j >= nfull) {  // exact zeros past T, whatever mx is
 #pragma unroll
       for (int e = 0; e < 16; ++e)
@@ -257,9 +264,9 @@ __device__ __forceinline__ uint4 block_keys_operand(const u32x2 (&R4)[4], int h)
 // at a time (S^T block j = K_j Q^T: a lane holds one query and half of the
 // block's keys), in two passes so that no lane holds a whole score row:
 //   pass 1: per lane, the running maximum m and the running sum l of
-//           exp(z - m) over its keys (z = half(S) * scale), rescaled when
+//           exp(scale (z - m)) over its keys (z = half(S)), rescaled when
 //           m grows; the two halves of a query's keys are then merged;
-//   pass 2: the same scores again, p = half(exp(z - M) / L) written to P
+//   pass 2: the same scores again, p = half(exp(scale (z - M)) / L) written to P
 //           and fed from registers to O^T += V_j^T P_j^T.
 // p differs from a single pass over the whole row only in the rounding of
 // the float32 sum L.
@@ -291,9 +298,10 @@ __global__ __launch_bounds__(NB * 64) void attn_fwd_kernel(const uint16_t* __res
   __syncthreads();
   const uint32_t kbase = lds_u32(sK), vbase = lds_u32(sV);
 
-  // z = half(S) * scale for the lane's 16 keys of block j (-inf past T;
-  // blocks below nfull have no key past T)
+  // z = half(S) for the lane's 16 keys of block j (-inf past T; blocks
+  // below nfull have no key past T); the scale is applied in the exponent
   const int nfull = T / 32;
+  const float c2 = scale * kLog2e;
   auto scores = [&](int j, float (&z)[16]) {
     f32x16 acc;
 #pragma unroll
@@ -304,8 +312,6 @@ __global__ __launch_bounds__(NB * 64) void attn_fwd_kernel(const uint16_t* __res
 #pragma unroll
     for (int e = 0; e < 16; e += 2) {
       unpack2<DT>(pack2<DT>(acc[e], acc[e + 1]), z[e], z[e + 1]);
-      z[e] *= scale;
-      z[e + 1] *= scale;
     }
     if (j >= nfull) {
 #pragma unroll
@@ -326,14 +332,14 @@ __global__ __launch_bounds__(NB * 64) void attn_fwd_kernel(const uint16_t* __res
     const float mn = fmaxf(m, bm);
     float t = 0.0f;
 #pragma unroll
-    for (int e = 0; e < 16; ++e) t += __expf(z[e] - mn);
-    l = (m == -INFINITY ? 0.0f : l * __expf(m - mn)) + t;
+    for (int e = 0; e < 16; ++e) t += exp_scaled(z[e] - mn, c2);
+    l = (m == -INFINITY ? 0.0f : l * exp_scaled(m - mn, c2)) + t;
     m = mn;
   }
   vst.store_clamped(sV, T, tid, NB * 64);
   __syncthreads();
   const float M = fmaxf(m, __shfl_xor(m, 32));  // finite: key 0 is in every row
-  const float lc = m == -INFINITY ? 0.0f : l * __expf(m - M);
+  const float lc = m == -INFINITY ? 0.0f : l * exp_scaled(m - M, c2);
   const float inv = 1.0f / (lc + __shfl_xor(lc, 32));
 
   // pass 2
@@ -349,7 +355,7 @@ __global__ __launch_bounds__(NB * 64) void attn_fwd_kernel(const uint16_t* __res
     u32x2 R4[4];
     float ex[16];
 #pragma unroll
-    for (int e = 0; e < 16; ++e) ex[e] = __expf(z[e] - M) * inv;
+    for (int e = 0; e < 16; ++e) ex[e] = exp_scaled(z[e] - M, c2) * inv;
     if (j >= nfull) {  // exact zeros past T, whatever M is
 #pragma unroll
       for (int e = 0; e < 16; ++e)
