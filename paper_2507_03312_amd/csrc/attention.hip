@@ -87,6 +87,13 @@ struct RowStage {
 constexpr float kLog2e = 1.4426950408889634f;
 __device__ __forceinline__ float exp_scaled(float x, float c2) { return __builtin_amdgcn_exp2f(x * c2); }
 
+// Accumulator entry e of key block j holds key 32 j + 8 (e / 4) + 4 hi + e % 4.
+// Only the last block (j = NB - 1) can have keys past T; its groups of 8 keys
+// that lie past T altogether are skipped (a uniform branch): at 65 tokens 3 of
+// 12 groups, at 197 tokens 3 of 28.  What they would add are exact zeros.
+__device__ __forceinline__ int key_of(int j, int e, int hi) { return 32 * j + 8 * (e >> 2) + 4 * hi + (e & 3); }
+__device__ __forceinline__ bool group_in(int j, int gq, int T) { return 32 * j + 8 * gq < T; }
+
 // Packs 4 halves.
 __device__ __forceinline__ u32x2 pack4(uint16_t a, uint16_t b, uint16_t c, uint16_t d) {
   return u32x2{a | ((uint32_t)b << 16), c | ((uint32_t)d << 16)};
@@ -186,37 +193,38 @@ __global__ __launch_bounds__(NB * 64) void attn_fwd_rows_kernel(const uint16_t* 
 
   // softmax over the keys of query q (float32; S rounded to half first)
   const float c2 = scale * kLog2e;
-  // (blocks below nfull have no key past T: no masks there)
-  const int nfull = T / 32;
   float mx = -INFINITY;
   static_for<NB>([&](auto j) {
 #pragma unroll
-    for (int e = 0; e < 16; e += 2) {
-      float a, c;
-      unpack2<DT>(pack2<DT>(s[j][e], s[j][e + 1]), a, c);
-      s[j][e] = a;
-      s[j][e + 1] = c;
-    }
-    if (j >= nfull) {
+    for (int gq = 0; gq < 4; ++gq) {
+      if (j == NB - 1 && !group_in(j, gq, T)) continue;
 #pragma unroll
-      for (int e = 0; e < 16; ++e)
-        if (32 * j + 8 * (e >> 2) + 4 * hi + (e & 3) >= T) s[j][e] = -INFINITY;
+      for (int e = 4 * gq; e < 4 * gq + 4; e += 2) {
+        float a, c;
+        unpack2<DT>(pack2<DT>(s[j][e], s[j][e + 1]), a, c);
+        s[j][e] = j == NB - 1 && key_of(j, e, hi) >= T ? -INFINITY : a;
+        s[j][e + 1] = j == NB - 1 && key_of(j, e + 1, hi) >= T ? -INFINITY : c;
+        mx = fmaxf(mx, fmaxf(s[j][e], s[j][e + 1]));
+      }
     }
-#pragma unroll
-    for (int e = 0; e < 16; ++e) mx = fmaxf(mx, s[j][e]);
   });
   mx = fmaxf(mx, __shfl_xor(mx, 32));
   float sum = 0.0f;
   static_for<NB>([&](auto j) {
 #pragma unroll
-    for (int e = 0; e < 16; ++e) s[j][e] = exp_scaled(s[j][e] - mx, c2);
-    if (j >= nfull) {  // exact zeros past T, whatever mx is
+    for (int gq = 0; gq < 4; ++gq) {
+      if (j == NB - 1 && !group_in(j, gq, T)) {
 #pragma unroll
-      for (int e = 0; e < 16; ++e)
-        if (32 * j + 8 * (e >> 2) + 4 * hi + (e & 3) >= T) s[j][e] = 0.0f;
+        for (int e = 4 * gq; e < 4 * gq + 4; ++e) s[j][e] = 0.0f;
+        continue;
+      }
+#pragma unroll
+      for (int e = 4 * gq; e < 4 * gq + 4; ++e) {
+        const float x = exp_scaled(s[j][e] - mx, c2);
+        s[j][e] = j == NB - 1 && key_of(j, e, hi) >= T ? 0.0f : x;  // exact zeros, whatever mx is
+        sum += s[j][e];
+      }
     }
-#pragma unroll
-    for (int e = 0; e < 16; ++e) sum += s[j][e];
   });
   sum += __shfl_xor(sum, 32);
   const float inv = 1.0f / sum;
@@ -239,6 +247,7 @@ __global__ __launch_bounds__(NB * 64) void attn_fwd_rows_kernel(const uint16_t* 
     for (int e = 0; e < 16; ++e) o[db][e] = 0.0f;
   uint16_t* prow = P + ((int64_t)bh * T + q) * ldP;
   static_for<2 * NB>([&](auto ks) {
+    if (ks == 2 * NB - 1 && 16 * ks >= T) return;  // no key (uniform)
     const uint4 bf = keys_operand<NB>(R, ks);  // keys 16 ks + 8 hi + 0..7
     if (q < T && 16 * ks + 8 * hi < ldP) *reinterpret_cast<uint4*>(prow + 16 * ks + 8 * hi) = bf;
 #pragma unroll
@@ -298,9 +307,8 @@ __global__ __launch_bounds__(NB * 64) void attn_fwd_kernel(const uint16_t* __res
   __syncthreads();
   const uint32_t kbase = lds_u32(sK), vbase = lds_u32(sV);
 
-  // z = half(S) for the lane's 16 keys of block j (-inf past T; blocks
-  // below nfull have no key past T); the scale is applied in the exponent
-  const int nfull = T / 32;
+  // z = half(S) for the lane's 16 keys of block j; the scale is applied in
+  // the exponent
   const float c2 = scale * kLog2e;
   auto scores = [&](int j, float (&z)[16]) {
     f32x16 acc;
@@ -310,31 +318,50 @@ __global__ __launch_bounds__(NB * 64) void attn_fwd_kernel(const uint16_t* __res
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk) acc = mfma32<DT>(lds_b128(row + 32 * kk), qf[kk], acc);
 #pragma unroll
-    for (int e = 0; e < 16; e += 2) {
-      unpack2<DT>(pack2<DT>(acc[e], acc[e + 1]), z[e], z[e + 1]);
-    }
-    if (j >= nfull) {
-#pragma unroll
-      for (int e = 0; e < 16; ++e)
-        if (32 * j + 8 * (e >> 2) + 4 * hi + (e & 3) >= T) z[e] = -INFINITY;
-    }
+    for (int e = 0; e < 16; e += 2) unpack2<DT>(pack2<DT>(acc[e], acc[e + 1]), z[e], z[e + 1]);
   };
 
   // pass 1
   float m = -INFINITY, l = 0.0f;
-  for (int j = 0; j < NB; ++j) {
+  for (int j = 0; j < NB - 1; ++j) {
     float z[16];
     scores(j, z);
     float bm = z[0];
 #pragma unroll
     for (int e = 1; e < 16; ++e) bm = fmaxf(bm, z[e]);
-    if (bm == -INFINITY) continue;  // every key of this half-block is past T
+    if (bm == -INFINITY) continue;
     const float mn = fmaxf(m, bm);
     float t = 0.0f;
 #pragma unroll
     for (int e = 0; e < 16; ++e) t += exp_scaled(z[e] - mn, c2);
     l = (m == -INFINITY ? 0.0f : l * exp_scaled(m - mn, c2)) + t;
     m = mn;
+  }
+  {  // the last block: groups past T skipped, -inf past T in the others
+    float z[16];
+    scores(NB - 1, z);
+    float bm = -INFINITY;
+#pragma unroll
+    for (int gq = 0; gq < 4; ++gq) {
+      if (!group_in(NB - 1, gq, T)) continue;
+#pragma unroll
+      for (int e = 4 * gq; e < 4 * gq + 4; ++e) {
+        if (key_of(NB - 1, e, hi) >= T) z[e] = -INFINITY;
+        bm = fmaxf(bm, z[e]);
+      }
+    }
+    if (bm != -INFINITY) {  // some key of this half-block is below T
+      const float mn = fmaxf(m, bm);
+      float t = 0.0f;
+#pragma unroll
+      for (int gq = 0; gq < 4; ++gq) {
+        if (!group_in(NB - 1, gq, T)) continue;
+#pragma unroll
+        for (int e = 4 * gq; e < 4 * gq + 4; ++e) t += exp_scaled(z[e] - mn, c2);
+      }
+      l = (m == -INFINITY ? 0.0f : l * exp_scaled(m - mn, c2)) + t;
+      m = mn;
+    }
   }
   vst.store_clamped(sV, T, tid, NB * 64);
   __syncthreads();
@@ -349,30 +376,46 @@ __global__ __launch_bounds__(NB * 64) void attn_fwd_kernel(const uint16_t* __res
 #pragma unroll
     for (int e = 0; e < 16; ++e) o[db][e] = 0.0f;
   uint16_t* prow = P + ((int64_t)bh * T + q) * ldP;
-  for (int j = 0; j < NB; ++j) {
+  // 16 keys (half hh of block j): P written, O^T += V^T P^T
+  auto keys16 = [&](int j, int hh, const u32x2 (&R4)[4]) {
+    const uint4 bf = block_keys_operand(R4, hh);  // keys 32 j + 16 hh + 8 hi + 0..7
+    const int key0 = 32 * j + 16 * hh + 8 * hi;
+    if (q < T && key0 < ldP) *reinterpret_cast<uint4*>(prow + key0) = bf;
+#pragma unroll
+    for (int db = 0; db < 2; ++db)
+      o[db] = mfma32<DT>(frag_tr(vbase, PD, 32 * j + 16 * hh, 32 * db, lane), bf, o[db]);
+  };
+  for (int j = 0; j < NB - 1; ++j) {
     float z[16];
     scores(j, z);
     u32x2 R4[4];
     float ex[16];
 #pragma unroll
     for (int e = 0; e < 16; ++e) ex[e] = exp_scaled(z[e] - M, c2) * inv;
-    if (j >= nfull) {  // exact zeros past T, whatever M is
-#pragma unroll
-      for (int e = 0; e < 16; ++e)
-        if (32 * j + 8 * (e >> 2) + 4 * hi + (e & 3) >= T) ex[e] = 0.0f;
-    }
 #pragma unroll
     for (int gq = 0; gq < 4; ++gq)
       R4[gq] = u32x2{pack2<DT>(ex[4 * gq], ex[4 * gq + 1]), pack2<DT>(ex[4 * gq + 2], ex[4 * gq + 3])};
+    keys16(j, 0, R4);
+    keys16(j, 1, R4);
+  }
+  {
+    float z[16];
+    scores(NB - 1, z);
+    u32x2 R4[4];
 #pragma unroll
-    for (int hh = 0; hh < 2; ++hh) {
-      const uint4 bf = block_keys_operand(R4, hh);  // keys 32 j + 16 hh + 8 hi + 0..7
-      const int key0 = 32 * j + 16 * hh + 8 * hi;
-      if (q < T && key0 < ldP) *reinterpret_cast<uint4*>(prow + key0) = bf;
+    for (int gq = 0; gq < 4; ++gq) {
+      R4[gq] = u32x2{0u, 0u};
+      if (!group_in(NB - 1, gq, T)) continue;
+      float ex[4];
 #pragma unroll
-      for (int db = 0; db < 2; ++db)
-        o[db] = mfma32<DT>(frag_tr(vbase, PD, 32 * j + 16 * hh, 32 * db, lane), bf, o[db]);
+      for (int c = 0; c < 4; ++c) {
+        const float x = exp_scaled(z[4 * gq + c] - M, c2) * inv;
+        ex[c] = key_of(NB - 1, 4 * gq + c, hi) >= T ? 0.0f : x;  // exact zeros past T, whatever M is
+      }
+      R4[gq] = u32x2{pack2<DT>(ex[0], ex[1]), pack2<DT>(ex[2], ex[3])};
     }
+    keys16(NB - 1, 0, R4);
+    if (group_in(NB - 1, 2, T)) keys16(NB - 1, 1, R4);
   }
   if (q < T) {
     uint16_t* out = O + ((int64_t)b * T + q) * dm + h * HD;
@@ -394,11 +437,12 @@ __global__ __launch_bounds__(NB * 64) void attn_fwd_kernel(const uint16_t* __res
 // Conversions go two values at a time.
 template <int DT, int NB>
 __device__ __forceinline__ void probs_to_ds_zero_padded(f32x16 (&dp)[NB], const u32x2 (&Pr)[NB][4],
-                                                        float scale, u32x2 (&Sr)[NB][4]) {
+                                                        float scale, int T, u32x2 (&Sr)[NB][4]) {
   float rs = 0.0f;
   static_for<NB>([&](auto j) {
 #pragma unroll
     for (int gq = 0; gq < 4; ++gq) {
+      if (j == NB - 1 && !group_in(j, gq, T)) continue;
       float p[4], d[4];
       unpack2<DT>(Pr[j][gq].x, p[0], p[1]);
       unpack2<DT>(Pr[j][gq].y, p[2], p[3]);
@@ -415,6 +459,10 @@ __device__ __forceinline__ void probs_to_ds_zero_padded(f32x16 (&dp)[NB], const 
   static_for<NB>([&](auto j) {
 #pragma unroll
     for (int gq = 0; gq < 4; ++gq) {
+      if (j == NB - 1 && !group_in(j, gq, T)) {
+        Sr[j][gq] = u32x2{0u, 0u};
+        continue;
+      }
       float p[4], ds[4];
       unpack2<DT>(Pr[j][gq].x, p[0], p[1]);
       unpack2<DT>(Pr[j][gq].y, p[2], p[3]);
@@ -428,12 +476,14 @@ __device__ __forceinline__ void probs_to_ds_zero_padded(f32x16 (&dp)[NB], const 
 // dQ^T = K^T dS^T for the wave's queries (K staged in LDS as [key][d]):
 // the float32 accumulators (lane = query, d in registers).
 template <int DT, int NB>
-__device__ __forceinline__ void bwd_dq_acc(uint32_t kbase, const u32x2 (&Sr)[NB][4], int lane, f32x16 (&o)[2]) {
+__device__ __forceinline__ void bwd_dq_acc(uint32_t kbase, const u32x2 (&Sr)[NB][4], int T, int lane,
+                                           f32x16 (&o)[2]) {
 #pragma unroll
   for (int db = 0; db < 2; ++db)
 #pragma unroll
     for (int e = 0; e < 16; ++e) o[db][e] = 0.0f;
   static_for<2 * NB>([&](auto ks) {
+    if (ks == 2 * NB - 1 && 16 * ks >= T) return;  // no key (uniform)
     const uint4 bf = keys_operand<NB>(Sr, ks);
 #pragma unroll
     for (int db = 0; db < 2; ++db) o[db] = mfma32<DT>(frag_tr(kbase, PD, 16 * ks, 32 * db, lane), bf, o[db]);
@@ -452,7 +502,7 @@ template <int DT, int NB>
 __device__ __forceinline__ void bwd_dq(uint32_t kbase, const u32x2 (&Sr)[NB][4], uint16_t* dQrow, int q,
                                        int T, int lane) {
   f32x16 o[2];
-  bwd_dq_acc<DT, NB>(kbase, Sr, lane, o);
+  bwd_dq_acc<DT, NB>(kbase, Sr, T, lane, o);
   if (q < T) put_dq_row<DT>(o, dQrow, lane);
 }
 
@@ -524,7 +574,7 @@ __device__ __forceinline__ void bwd_query_block_zp(const uint16_t* V, int64_t ld
     }
     dp[j] = acc;
   });
-  probs_to_ds_zero_padded<DT, NB>(dp, Pr, scale, Sr);
+  probs_to_ds_zero_padded<DT, NB>(dp, Pr, scale, T, Sr);
 }
 
 // T <= 128: the whole backward of one (batch, head) in one workgroup.
@@ -588,6 +638,7 @@ __global__ __launch_bounds__(NB * 64) void attn_bwd_kernel(const uint16_t* __res
 #pragma unroll
     for (int e = 0; e < 16; ++e) dk[db][e] = dv[db][e] = 0.0f;
   static_for<2 * NB>([&](auto ks) {
+    if (ks == 2 * NB - 1 && 16 * ks >= T) return;  // no query (uniform)
     const uint4 sa = frag_tr(sbase, PK, 16 * ks, 32 * w, lane);
     const uint4 pa = frag_tr(pbase, PK, 16 * ks, 32 * w, lane);
 #pragma unroll
@@ -718,11 +769,11 @@ __global__ __launch_bounds__(NB * 64) void attn_bwd_fused_kernel(const uint16_t*
         if (!(q < T && 32 * j + 8 * gq + 4 * hi < T)) Pr[j][gq] = u32x2{0u, 0u};
       }
     });
-    probs_to_ds_zero_padded<DT, NB>(dp, Pr, scale, Sr);
+    probs_to_ds_zero_padded<DT, NB>(dp, Pr, scale, T, Sr);
   }
   if constexpr (kStage) {
     f32x16 o[2];
-    bwd_dq_acc<DT, NB>(kbase, Sr, lane, o);
+    bwd_dq_acc<DT, NB>(kbase, Sr, T, lane, o);
     put_dq_row<DT>(o, stage + (lane & 31) * OP, lane);
     copy_rows_out(stage, dQ + 32 * w * ld, ld, nrows, lane);
   } else {
@@ -755,6 +806,7 @@ __global__ __launch_bounds__(NB * 64) void attn_bwd_fused_kernel(const uint16_t*
     const uint32_t pbase = (r & 1) ? vbase : kbase, sbase = pbase + 32 * PK * 2;
 #pragma unroll
     for (int ks = 0; ks < 2; ++ks) {
+      if (ks == 1 && 32 * r + 16 >= T) continue;  // no query (uniform)
       const uint4 sa = frag_tr(sbase, PK, 16 * ks, 32 * w, lane);
       const uint4 pa = frag_tr(pbase, PK, 16 * ks, 32 * w, lane);
 #pragma unroll
