@@ -70,13 +70,15 @@ struct RowStage {
       v[i] = *reinterpret_cast<const u32x4*>(src + min(c >> 3, T - 1) * ld + (c & 7) * 8);
     }
   }
+  // R: rows of the LDS array (the rows from there on are dropped)
+  template <int R = 1 << 20>
   __device__ __forceinline__ void store_clamped(uint16_t* lds, int T, int tid, int nthreads) {
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
       const int c = tid + i * nthreads;
       asm volatile("" : "+v"(v[i]));  // keeps the load unconditional
       if ((c >> 3) >= T) v[i] = u32x4{0u, 0u, 0u, 0u};
-      *reinterpret_cast<u32x4*>(lds + (c >> 3) * PD + (c & 7) * 8) = v[i];
+      if ((c >> 3) < R) *reinterpret_cast<u32x4*>(lds + (c >> 3) * PD + (c & 7) * 8) = v[i];
     }
   }
 };
@@ -577,23 +579,34 @@ __device__ __forceinline__ void bwd_query_block_zp(const uint16_t* V, int64_t ld
   probs_to_ds_zero_padded<DT, NB>(dp, Pr, scale, T, Sr);
 }
 
-// T <= 128: the whole backward of one (batch, head) in one workgroup.
-template <int DT, int NB>
-__global__ __launch_bounds__(NB * 64) void attn_bwd_kernel(const uint16_t* __restrict__ qkv,
+// T <= 128: the whole backward of one (batch, head) in one workgroup.  R: T
+// rounded up to 16, the rows kept in LDS.  What bounds it is latency: a
+// workgroup loads, multiplies and stores in turn, so the workgroups a CU
+// holds overlap those phases, and LDS decides how many it holds.  The P and dS
+// arrays therefore take K's place once dQ is done, and R rows are kept instead
+// of whole blocks of 32: 51 KB at 65 tokens (3 workgroups per CU) where
+// separate arrays of 96 rows took 81 KB (2).
+template <int DT, int R>
+__global__ __launch_bounds__((R + 31) / 32 * 64)
+// 9 waves per CU at R = 80: one SIMD holds three
+__attribute__((amdgpu_waves_per_eu(R == 80 ? 3 : 1)))
+void attn_bwd_kernel(const uint16_t* __restrict__ qkv,
                                                            const uint16_t* __restrict__ P,
                                                            const uint16_t* __restrict__ dO,
                                                            uint16_t* __restrict__ dqkv, int T, int H,
                                                            int ldP, float scale) {
-  constexpr int TK = 32 * NB;
+  constexpr int NB = (R + 31) / 32;
   // pitch (halves) of the [query][key] arrays: 4 consecutive rows of a
-  // transposed read land in distinct banks, and at T <= 96 the whole LDS
-  // footprint stays under 80 KiB, so two workgroups share a CU
-  constexpr int PK = TK + 8;
-  __shared__ __attribute__((aligned(16))) uint16_t sK[TK * PD];
-  __shared__ __attribute__((aligned(16))) uint16_t sQ[TK * PD];
-  __shared__ __attribute__((aligned(16))) uint16_t sdO[TK * PD];
-  __shared__ __attribute__((aligned(16))) uint16_t sP[TK * PK];
-  __shared__ __attribute__((aligned(16))) uint16_t sdS[TK * PK];
+  // transposed read land in distinct banks.  The last key block's reads may
+  // run past a row's end (keys >= T, whose results are not stored): into the
+  // next row, or behind the last row into the slack of 32 halves
+  constexpr int PK = R + 8;
+  constexpr int KPS = R * PD > 2 * R * PK + 32 ? R * PD : 2 * R * PK + 32;
+  __shared__ __attribute__((aligned(16))) uint16_t sQ[R * PD];
+  __shared__ __attribute__((aligned(16))) uint16_t sdO[R * PD];
+  __shared__ __attribute__((aligned(16))) uint16_t sK[KPS];  // K, then P and dS
+  uint16_t* sP = sK;
+  uint16_t* sdS = sK + R * PK;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int bh = blockIdx.x, b = bh / H, h = bh % H;
   const int dm = H * HD;
@@ -609,26 +622,31 @@ __global__ __launch_bounds__(NB * 64) void attn_bwd_kernel(const uint16_t* __res
     kst.load_clamped(K, ld, T, tid, NB * 64);
     qst.load_clamped(Q, ld, T, tid, NB * 64);
     gst.load_clamped(G, dm, T, tid, NB * 64);
-    kst.store_clamped(sK, T, tid, NB * 64);
-    qst.store_clamped(sQ, T, tid, NB * 64);
-    gst.store_clamped(sdO, T, tid, NB * 64);
+    kst.template store_clamped<R>(sK, T, tid, NB * 64);
+    qst.template store_clamped<R>(sQ, T, tid, NB * 64);
+    gst.template store_clamped<R>(sdO, T, tid, NB * 64);
   }
 
   const int q = 32 * w + (lane & 31);
   u32x2 Pr[NB][4], Sr[NB][4];
   bwd_query_block_zp<DT, NB>(V, ld, G, dm, P + (int64_t)bh * T * ldP, ldP, q, T, scale, lane, Pr, Sr);
-  // the [query][key] copies for the dK / dV products (rows >= T are 0)
-  static_for<NB>([&](auto j) {
-#pragma unroll
-    for (int gq = 0; gq < 4; ++gq) {
-      const int key0 = 32 * j + 8 * gq + 4 * (lane >> 5);
-      *reinterpret_cast<u32x2*>(sP + q * PK + key0) = Pr[j][gq];
-      *reinterpret_cast<u32x2*>(sdS + q * PK + key0) = Sr[j][gq];
-    }
-  });
-  __syncthreads();  // sK / sQ / sdO staged, sP / sdS complete
+  __syncthreads();  // sK / sQ / sdO staged
 
   bwd_dq<DT, NB>(lds_u32(sK), Sr, dQ + q * ld, q, T, lane);
+  __syncthreads();  // sK is read
+  // the [query][key] copies for the dK / dV products (rows T..R-1 are 0)
+  if (q < R) {
+    static_for<NB>([&](auto j) {
+#pragma unroll
+      for (int gq = 0; gq < 4; ++gq) {
+        if (32 * j + 8 * gq >= R) continue;  // compile time
+        const int key0 = 32 * j + 8 * gq + 4 * (lane >> 5);
+        *reinterpret_cast<u32x2*>(sP + q * PK + key0) = Pr[j][gq];
+        *reinterpret_cast<u32x2*>(sdS + q * PK + key0) = Sr[j][gq];
+      }
+    });
+  }
+  __syncthreads();  // sP / sdS complete
 
   // per key block (wave w): dK = dS^T Q and dV = P^T dO over all queries
   const uint32_t qbase = lds_u32(sQ), gbase = lds_u32(sdO), pbase = lds_u32(sP), sbase = lds_u32(sdS);
@@ -637,8 +655,7 @@ __global__ __launch_bounds__(NB * 64) void attn_bwd_kernel(const uint16_t* __res
   for (int db = 0; db < 2; ++db)
 #pragma unroll
     for (int e = 0; e < 16; ++e) dk[db][e] = dv[db][e] = 0.0f;
-  static_for<2 * NB>([&](auto ks) {
-    if (ks == 2 * NB - 1 && 16 * ks >= T) return;  // no query (uniform)
+  static_for<R / 16>([&](auto ks) {  // queries 16 ks..: T > R - 16, none of them wholly past T
     const uint4 sa = frag_tr(sbase, PK, 16 * ks, 32 * w, lane);
     const uint4 pa = frag_tr(pbase, PK, 16 * ks, 32 * w, lane);
 #pragma unroll
@@ -853,18 +870,26 @@ template <int DT>
 hipError_t launch_bwd(const uint16_t* qkv, const uint16_t* P, const uint16_t* dO, uint16_t* dqkv, int B,
                       int T, int H, int ldP, float scale, hipStream_t s) {
   const dim3 grid((unsigned)(B * H));
-  const int nb = (T + 31) / 32;
-#define MPX_B(NBv) attn_bwd_kernel<DT, NBv><<<grid, NBv * 64, 0, s>>>(qkv, P, dO, dqkv, T, H, ldP, scale)
+#define MPX_B(Rv) attn_bwd_kernel<DT, Rv><<<grid, (Rv + 31) / 32 * 64, 0, s>>>(qkv, P, dO, dqkv, T, H, ldP, scale)
 #define MPX_B2(NBv) attn_bwd_fused_kernel<DT, NBv><<<grid, NBv * 64, 0, s>>>(qkv, P, dO, dqkv, T, H, ldP, scale)
-  switch (nb) {
-    case 1: MPX_B(1); break;
-    case 2: MPX_B(2); break;
-    case 3: MPX_B(3); break;
-    case 4: MPX_B(4); break;
-    case 5: MPX_B2(5); break;
-    case 6: MPX_B2(6); break;
-    case 7: MPX_B2(7); break;
-    default: MPX_B2(8); break;
+  if (T <= 128) {
+    switch ((T + 15) / 16) {
+      case 1: MPX_B(16); break;
+      case 2: MPX_B(32); break;
+      case 3: MPX_B(48); break;
+      case 4: MPX_B(64); break;
+      case 5: MPX_B(80); break;
+      case 6: MPX_B(96); break;
+      case 7: MPX_B(112); break;
+      default: MPX_B(128); break;
+    }
+  } else {
+    switch ((T + 31) / 32) {
+      case 5: MPX_B2(5); break;
+      case 6: MPX_B2(6); break;
+      case 7: MPX_B2(7); break;
+      default: MPX_B2(8); break;
+    }
   }
 #undef MPX_B
 #undef MPX_B2

@@ -126,6 +126,15 @@ def test_fused_attention(fmt, bth):
     _check_bwd(pol, fmt, qkv, dout, B, T, H, gP, gdq)
 
 
+@pytest.mark.parametrize("T", [8, 16, 17, 31, 48, 49, 64, 80, 81, 96, 112, 113, 120, 136, 145, 177, 209, 241])
+def test_fused_attention_group_edges(T):
+    """Lengths at the edges of the groups of 8 keys and steps of 16 rows that
+    the kernels skip or do not keep past T."""
+    pol, qkv, dout, gO, gPfull, gdq = _run(2, T, 3, "bf16", seed=T)
+    _, _, _, gP = _check_fwd(pol, "bf16", qkv, 2, T, 3, gO, gPfull)
+    _check_bwd(pol, "bf16", qkv, dout, 2, T, 3, gP, gdq)
+
+
 @pytest.mark.parametrize("fmt,bth", [("bf16", (128, 6, 65)), ("f16", (256, 6, 65)), ("bf16", (64, 12, 197))],
                          ids=lambda s: str(s))
 def test_fused_attention_full_size(fmt, bth):
