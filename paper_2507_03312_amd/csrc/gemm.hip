@@ -242,9 +242,9 @@ static int linear_bwd(const char* fn, const void* X, const void* W, const void* 
       // the GEMM wrote splits x (K / 128 tile columns) bias partials per row
       const int64_t MN = N * K, nrows = db_fused ? N : 0;
       const int dbparts = (int)(db_partials_count(sp, N, K) / N);
-      // 4 outputs per thread from 4 splits on (ViT-S, 8-16 splits: step +1.4%);
-      // with 2 or 3 the one-output form measured 0.2-0.3% faster in the ViT-B step
-      const bool vec = g.splits >= 4 && splitk_reduce_vec(g.ws, MN, (const uint16_t*)dW);
+      // 4 outputs per thread wherever the rows allow (from 4 splits on only, as
+      // before, the ViT-B step measured 1.5% slower: its MLP gradients have 3)
+      const bool vec = splitk_reduce_vec(g.ws, MN, (const uint16_t*)dW);
       const unsigned blocks = splitk_reduce_blocks(MN, nrows, vec);
 #define MPX_SKR(DTv, VECv)                                                                       \
   splitk_reduce_kernel<DTv, VECv><<<blocks, 256, 0, s>>>(g.ws, g.splits, MN, (uint16_t*)dW, d_nonfinite, \
