@@ -8,13 +8,11 @@
 //   forward  Y  = X W^T   : A = X  k-major,  B = W  k-major
 //   backward dX = dY W    : A = dY k-major,  B = W  mn-major
 //   backward dW = dY^T X  : A = dY mn-major, B = X  mn-major
-// Tiles are staged through LDS in one layout, [row][k] with k contiguous, so
-// the MFMA operand reads are always 16-byte ds_read_b128.  An mn-major operand
-// is transposed on the way in: each lane loads 4 rows of 8 contiguous values
-// and writes them as 8 rows of 4 k-values (a register transpose of 16-bit
-// pairs).  The MFMA is v_mfma_f32_32x32x16_{f16,bf16}: lane l holds 8 k-values
-// of row l%32 for A and of column l%32 for B; the 16 accumulators of lane l are
-// column l%32, rows 8*(i/4) + 4*(l/32) + i%4.
+// Tiles lie in LDS as they lie in memory; k-major fragments are read with
+// ds_read_b128, mn-major ones with transposing reads.  The MFMA is
+// v_mfma_f32_32x32x16_{f16,bf16}: lane l holds 8 k-values of row l%32 for A and
+// of column l%32 for B; its operands are swapped, so the 16 accumulators of lane
+// l are row l%32, columns 8*(i/4) + 4*(l/32) + i%4.
 //
 // Epilogue (all optional, in this order, each rounding once to half):
 //   h = half(acc + bias[n]);  pre_out = h;  h = half(gelu(h));
@@ -51,11 +49,9 @@ struct GemmArgs {
   uint16_t* pre;
   const uint16_t* dact;
   int32_t act;
-  int32_t full_epi;  // set by the dispatcher: whole tiles may use gemm_epilogue_lds
+  int32_t full_epi;  // set by the dispatcher: every epilogue operand is 16-byte aligned
   // if set, the number of non-finite half outputs C is added to *nonfinite
-  // (split-K partials are counted by the reduction that rounds them
-  // instead); such calls take the generic epilogue or the whole-tile one
-  // compiled with EPI_COUNT
+  // (split-K partials are counted by the reduction that rounds them instead)
   int32_t* nonfinite;
   // weight-gradient products (both operands mn-major) may also return the
   // bias gradient db[m] = half(sum_k A(m, k)), summed from the A fragments
@@ -66,11 +62,9 @@ struct GemmArgs {
   float* dbp;
 };
 
-// Epilogue variants chosen at compile time (a mask of these bits), used for
-// tiles that lie wholly inside the output when every epilogue operand is
-// 8-byte aligned: no per-element masks, no runtime flag tests, one 64-bit
-// base per wave and 32-bit lane offsets.  The arithmetic is the generic
-// epilogue's, step for step, so both give identical bits.
+// Epilogue operations compiled into a kernel (a mask of these bits);
+// EPI_GENERIC takes them from the call's arguments, the same arithmetic step
+// for step.
 // EPI_COUNT: add the number of non-finite outputs to g.nonfinite (weight
 // gradients, which have no other epilogue operation)
 enum : int { EPI_BIAS = 1, EPI_GELU = 2, EPI_DACT = 4, EPI_RESID = 8, EPI_COUNT = 16,
@@ -276,24 +270,22 @@ __device__ __forceinline__ void gemm_partials(const GemmArgs& g, const f32x16 (&
 //
 // The main loop of the kernel below moves operand tiles from global memory
 // straight into LDS (global_load_lds_dwordx4: each lane's 16 bytes land at
-// M0 + 16 * lane, so one wave instruction fills 1 KiB of LDS) and keeps
-// S - 1 k tiles of 64 in flight while the MFMAs consume the oldest one.  No
-// registers stage the tiles, so deep pipelines cost LDS only.  The compiler
-// does not track these copies: each k step waits for its own tile with an
-// explicit vmcnt and one barrier makes the tile visible to every wave.
+// M0 + 16 * lane, so one wave instruction fills 1 KiB of LDS).  The compiler
+// does not track these copies: an explicit vmcnt waits for a k tile, and one
+// barrier makes it visible to every wave.
 //
 // LDS layouts (no padding: a copy fills 1 KiB contiguously, so bank
 // conflicts are avoided by permuting 16-byte chunks instead):
 //   k-major operand   [row][64 k], 128 B per row; chunk c of row r sits at
 //                     position c ^ ((r >> 1) & 7).  The 16 lanes reading one
 //                     ds_read_b128 phase (16 rows, one chunk) hit all 64 banks.
-//   mn-major operand  [k][ROWS] (ROWS = 128 or 256 outputs, 16 or 32 chunks
-//                     per k row); chunk c of k row kr sits at c ^ (4*(kr & 3)).
+//   mn-major operand  [k][ROWS] (64 to 256 outputs, 8 to 32 chunks per k
+//                     row), chunks permuted by dma_chunk.
 //                     MFMA fragments are read with ds_read_b64_tr_b16, which
 //                     transposes 16-bit elements across groups of 16 lanes, so
 //                     the operand needs no transposition on the way in.
-// Requirements (checked by the dispatcher): 16-byte aligned operands with
-// leading dimensions and batch strides that are multiples of 8, and every
+// Requirements of the copies (checked by the dispatcher; other operands go
+// through StagedOperand): 16-byte aligned operands with leading dimensions and batch strides that are multiples of 8, and every
 // split's k range a multiple of 64.  Rows past M or N read clamped (valid)
 // addresses; their results are never stored.
 
