@@ -323,20 +323,24 @@ __global__ __launch_bounds__(NB * 64) void attn_fwd_kernel(const uint16_t* __res
     for (int e = 0; e < 16; e += 2) unpack2<DT>(pack2<DT>(acc[e], acc[e + 1]), z[e], z[e + 1]);
   };
 
-  // pass 1
+  // pass 1.  fmaxf drops a NaN, so only the sum l carries it to the row: every
+  // score is added to l, also where the maximum is still -inf (0 stands in for
+  // it: exp(-inf) = 0 and exp(NaN) = NaN), and l is kept, not cleared, when the
+  // first finite score arrives.
   float m = -INFINITY, l = 0.0f;
+  auto base = [](float mx) { return mx == -INFINITY ? 0.0f : mx; };
+  auto rescaled = [&](float mn) { return m == -INFINITY ? l : l * exp_scaled(m - mn, c2); };
   for (int j = 0; j < NB - 1; ++j) {
     float z[16];
     scores(j, z);
     float bm = z[0];
 #pragma unroll
     for (int e = 1; e < 16; ++e) bm = fmaxf(bm, z[e]);
-    if (bm == -INFINITY) continue;
-    const float mn = fmaxf(m, bm);
+    const float mn = fmaxf(m, bm), mb = base(mn);
     float t = 0.0f;
 #pragma unroll
-    for (int e = 0; e < 16; ++e) t += exp_scaled(z[e] - mn, c2);
-    l = (m == -INFINITY ? 0.0f : l * exp_scaled(m - mn, c2)) + t;
+    for (int e = 0; e < 16; ++e) t += exp_scaled(z[e] - mb, c2);
+    l = rescaled(mn) + t;
     m = mn;
   }
   {  // the last block: groups past T skipped, -inf past T in the others
@@ -352,23 +356,21 @@ __global__ __launch_bounds__(NB * 64) void attn_fwd_kernel(const uint16_t* __res
         bm = fmaxf(bm, z[e]);
       }
     }
-    if (bm != -INFINITY) {  // some key of this half-block is below T
-      const float mn = fmaxf(m, bm);
-      float t = 0.0f;
+    const float mn = fmaxf(m, bm), mb = base(mn);
+    float t = 0.0f;
 #pragma unroll
-      for (int gq = 0; gq < 4; ++gq) {
-        if (!group_in(NB - 1, gq, T)) continue;
+    for (int gq = 0; gq < 4; ++gq) {
+      if (!group_in(NB - 1, gq, T)) continue;
 #pragma unroll
-        for (int e = 4 * gq; e < 4 * gq + 4; ++e) t += exp_scaled(z[e] - mn, c2);
-      }
-      l = (m == -INFINITY ? 0.0f : l * exp_scaled(m - mn, c2)) + t;
-      m = mn;
+      for (int e = 4 * gq; e < 4 * gq + 4; ++e) t += exp_scaled(z[e] - mb, c2);
     }
+    l = rescaled(mn) + t;
+    m = mn;
   }
   vst.store_clamped(sV, T, tid, NB * 64);
   __syncthreads();
-  const float M = fmaxf(m, __shfl_xor(m, 32));  // finite: key 0 is in every row
-  const float lc = m == -INFINITY ? 0.0f : l * exp_scaled(m - M, c2);
+  const float M = fmaxf(m, __shfl_xor(m, 32));
+  const float lc = rescaled(M);
   const float inv = 1.0f / (lc + __shfl_xor(lc, 32));
 
   // pass 2

@@ -153,3 +153,51 @@ def test_fused_attention_limits():
         mx.mpx_attention_bwd(t.data_ptr(), t.data_ptr(), t.data_ptr(), t.data_ptr(), 1, 8, 1, 32,
                              mx.MPX_BF16, None, 0, _s())
 
+
+
+def _run_fwd(qkv, B, T, H, fmt):
+    tq = to_dev_half(qkv, fmt)
+    tO, tP = _empty((B * T, H * HD), fmt), _empty((B * H * T, -(-T // 8) * 8), fmt)
+    mx.mpx_attention_fwd(tq.data_ptr(), tO.data_ptr(), tP.data_ptr(), B, T, H, HD, mx.DTYPES[fmt], _s())
+    return to_host(tO), to_host(tP).reshape(B, H, T, -1)
+
+
+@pytest.mark.parametrize("T,keys", [(16, [3]), (64, range(32, 64)), (160, range(0, 32)), (160, range(128, 160)),
+                                    (161, [160]), (192, [40]), (197, [196]), (197, range(192, 197)),
+                                    (256, range(224, 256)), (256, [0, 4, 255])], ids=str)
+def test_nan_scores_reach_the_whole_row(T, keys):
+    """NaN keys (one, the last of a ragged block, a whole block) make every
+    probability of every query NaN, as a softmax over the row does, so a
+    row's finite entries never hide an overflow."""
+    qkv, _ = _inputs(1, T, 2, "bf16", seed=T)
+    qkv = np.array(qkv)
+    qkv[list(keys), 2 * HD:4 * HD] = np.nan  # K of both heads
+    gO, gP = _run_fwd(qkv, 1, T, 2, "bf16")
+    assert np.all(np.isnan(gP[..., :T])) and np.all(gP[..., T:] == 0.0)
+    assert np.all(np.isnan(gO))
+
+
+@pytest.mark.parametrize("T,keys", [(64, range(0, 32)), (160, range(0, 32)), (160, range(128, 160)), (197, range(0, 64)),
+                                    (197, range(192, 197)), (256, range(0, 224))], ids=str)
+def test_overflowed_scores_are_zero_probabilities(T, keys):
+    """Scores that overflow to -inf in half (whole blocks of keys, first or
+    last) give probabilities of exactly 0 and leave the other keys' softmax as
+    it is."""
+    fmt, keys = "f16", list(keys)
+    qkv, _ = _inputs(1, T, 1, fmt, seed=T)
+    qkv = np.array(qkv)
+    qkv[:, 0], qkv[:, HD] = 200.0, 0.0
+    qkv[keys, HD] = -400.0  # 200 * -400 lies below the smallest half
+    gO, gP = _run_fwd(qkv, 1, T, 1, fmt)
+    pol = Policy(fmt)
+    q, k, v = ops.split_heads(qkv, 1, T, 1, HD)
+    kt = np.swapaxes(k, -1, -2)
+    S = np.asarray(pol.R(pol.mm(q, kt)), np.float64)
+    assert np.all(np.isneginf(S[..., keys]))
+    e = np.exp((S - S.max(-1, keepdims=True)) / 8.0)
+    P = e / e.sum(-1, keepdims=True)
+    dS = np.where(np.isfinite(S), ulp(np.where(np.isfinite(S), S, 0.0), fmt) + 2 * HD * 2.0 ** -24 * (_abs(q) @ _abs(kt)), 0.0)
+    bP = P / 8.0 * (dS + (P * dS).sum(-1, keepdims=True)) * 1.1 + P * 2.0 ** -18 + ulp(P, fmt)
+    assert np.all(gP[..., keys] == 0.0)
+    assert_within(gP[..., :T], P, bP, "P")
+    assert np.all(np.isfinite(gO))
