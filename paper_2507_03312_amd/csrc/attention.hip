@@ -90,9 +90,10 @@ constexpr float kLog2e = 1.4426950408889634f;
 __device__ __forceinline__ float exp_scaled(float x, float c2) { return __builtin_amdgcn_exp2f(x * c2); }
 
 // Accumulator entry e of key block j holds key 32 j + 8 (e / 4) + 4 hi + e % 4.
-// Only the last block (j = NB - 1) can have keys past T; its groups of 8 keys
-// that lie past T altogether are skipped (a uniform branch): at 65 tokens 3 of
-// 12 groups, at 197 tokens 3 of 28.  What they would add are exact zeros.
+// Only the last block (j = NB - 1) can have keys past T; groups of 8 keys that
+// lie past T altogether are skipped (at 65 tokens 2 of 12 groups, at 197 tokens 2
+// of 28; the long backward, by a uniform branch, 3).  What they would add are
+// exact zeros.
 __device__ __forceinline__ int key_of(int j, int e, int hi) { return 32 * j + 8 * (e >> 2) + 4 * hi + (e & 3); }
 __device__ __forceinline__ bool group_in(int j, int gq, int T) { return 32 * j + 8 * gq < T; }
 
@@ -158,12 +159,19 @@ __device__ __forceinline__ uint4 keys_operand(const u32x2 (&R)[NB][4], int ks) {
 // query's whole score row in registers (K read straight from global memory).
 // It measured faster there than the two-pass kernel below (13.8-15.1 vs
 // 16.6-17.4 us at 65 tokens, batch 128, 6 heads).
-template <int DT, int NB>
+// LAST (both forward kernels): the keys of the last block that are worked on, 16
+// or 32 with those past T masked, or 0 when T = 32 NB and nothing is tested.
+// Compile time, because a run time branch per group of 8 keys keeps the groups'
+// exponentials from overlapping (256 workgroups, us with the branches / without:
+// 32 tokens 4.1 / 3.3, 60 tokens 5.1 / 4.6, 96 tokens 7.1 / 6.3, 45 tokens
+// 4.3 / 3.9).
+template <int DT, int NB, int LAST>
 __global__ __launch_bounds__(NB * 64) void attn_fwd_rows_kernel(const uint16_t* __restrict__ qkv,
                                                            uint16_t* __restrict__ O,
-                                                           uint16_t* __restrict__ P, int T, int H,
+                                                           uint16_t* __restrict__ P, int Targ, int H,
                                                            int ldP, float scale) {
   constexpr int TK = 32 * NB;
+  const int T = LAST ? Targ : TK;
   __shared__ __attribute__((aligned(16))) uint16_t sV[TK * PD];
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, hi = lane >> 5;
   const int bh = blockIdx.x, b = bh / H, h = bh % H;
@@ -193,39 +201,35 @@ __global__ __launch_bounds__(NB * 64) void attn_fwd_rows_kernel(const uint16_t* 
     s[j] = acc;
   });
 
-  // softmax over the keys of query q (float32; S rounded to half first)
+  // softmax over the keys of query q (float32; S rounded to half first).  Entry e
+  // of block j is masked where its key is past T, and beyond LAST not looked at
+  auto masked = [&](int j, int e) { return LAST != 0 && j == NB - 1 && key_of(j, e, hi) >= T; };
+  auto beyond = [](int j, int e) { return LAST == 16 && j == NB - 1 && e >= 8; };
   const float c2 = scale * kLog2e;
   float mx = -INFINITY;
   static_for<NB>([&](auto j) {
 #pragma unroll
-    for (int gq = 0; gq < 4; ++gq) {
-      if (j == NB - 1 && !group_in(j, gq, T)) continue;
-#pragma unroll
-      for (int e = 4 * gq; e < 4 * gq + 4; e += 2) {
-        float a, c;
-        unpack2<DT>(pack2<DT>(s[j][e], s[j][e + 1]), a, c);
-        s[j][e] = j == NB - 1 && key_of(j, e, hi) >= T ? -INFINITY : a;
-        s[j][e + 1] = j == NB - 1 && key_of(j, e + 1, hi) >= T ? -INFINITY : c;
-        mx = fmaxf(mx, fmaxf(s[j][e], s[j][e + 1]));
-      }
+    for (int e = 0; e < 16; e += 2) {
+      if (beyond(j, e)) continue;
+      float a, c;
+      unpack2<DT>(pack2<DT>(s[j][e], s[j][e + 1]), a, c);
+      s[j][e] = masked(j, e) ? -INFINITY : a;
+      s[j][e + 1] = masked(j, e + 1) ? -INFINITY : c;
+      mx = fmaxf(mx, fmaxf(s[j][e], s[j][e + 1]));
     }
   });
   mx = fmaxf(mx, __shfl_xor(mx, 32));
   float sum = 0.0f;
   static_for<NB>([&](auto j) {
 #pragma unroll
-    for (int gq = 0; gq < 4; ++gq) {
-      if (j == NB - 1 && !group_in(j, gq, T)) {
-#pragma unroll
-        for (int e = 4 * gq; e < 4 * gq + 4; ++e) s[j][e] = 0.0f;
+    for (int e = 0; e < 16; ++e) {
+      if (beyond(j, e)) {
+        s[j][e] = 0.0f;
         continue;
       }
-#pragma unroll
-      for (int e = 4 * gq; e < 4 * gq + 4; ++e) {
-        const float x = exp_scaled(s[j][e] - mx, c2);
-        s[j][e] = j == NB - 1 && key_of(j, e, hi) >= T ? 0.0f : x;  // exact zeros, whatever mx is
-        sum += s[j][e];
-      }
+      const float x = exp_scaled(s[j][e] - mx, c2);
+      s[j][e] = masked(j, e) ? 0.0f : x;  // exact zeros, whatever mx is
+      sum += s[j][e];
     }
   });
   sum += __shfl_xor(sum, 32);
@@ -249,7 +253,7 @@ __global__ __launch_bounds__(NB * 64) void attn_fwd_rows_kernel(const uint16_t* 
     for (int e = 0; e < 16; ++e) o[db][e] = 0.0f;
   uint16_t* prow = P + ((int64_t)bh * T + q) * ldP;
   static_for<2 * NB>([&](auto ks) {
-    if (ks == 2 * NB - 1 && 16 * ks >= T) return;  // no key (uniform)
+    if (LAST == 16 && ks == 2 * NB - 1) return;  // no key
     const uint4 bf = keys_operand<NB>(R, ks);  // keys 16 ks + 8 hi + 0..7
     if (q < T && 16 * ks + 8 * hi < ldP) *reinterpret_cast<uint4*>(prow + 16 * ks + 8 * hi) = bf;
 #pragma unroll
@@ -281,12 +285,15 @@ __device__ __forceinline__ uint4 block_keys_operand(const u32x2 (&R4)[4], int h)
 //           and fed from registers to O^T += V_j^T P_j^T.
 // p differs from a single pass over the whole row only in the rounding of
 // the float32 sum L.
-template <int DT, int NB>
+template <int DT, int NB, int LAST>
 __global__ __launch_bounds__(NB * 64) void attn_fwd_kernel(const uint16_t* __restrict__ qkv,
                                                            uint16_t* __restrict__ O,
-                                                           uint16_t* __restrict__ P, int T, int H,
+                                                           uint16_t* __restrict__ P, int Targ, int H,
                                                            int ldP, float scale) {
   constexpr int TK = 32 * NB;
+  const int T = LAST ? Targ : TK;
+  constexpr int kWhole = LAST ? NB - 1 : NB;  // blocks without a key past T
+  constexpr int kGroups = LAST / 8;           // groups of 8 keys of the last block worked on
   __shared__ __attribute__((aligned(16))) uint16_t sK[TK * PD];
   __shared__ __attribute__((aligned(16))) uint16_t sV[TK * PD];
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, hi = lane >> 5;
@@ -330,7 +337,9 @@ __global__ __launch_bounds__(NB * 64) void attn_fwd_kernel(const uint16_t* __res
   float m = -INFINITY, l = 0.0f;
   auto base = [](float mx) { return mx == -INFINITY ? 0.0f : mx; };
   auto rescaled = [&](float mn) { return m == -INFINITY ? l : l * exp_scaled(m - mn, c2); };
-  for (int j = 0; j < NB - 1; ++j) {
+  // (both passes two blocks at a time: 640 workgroups of 224 tokens 41.6 -> 40.7 us)
+#pragma unroll 2
+  for (int j = 0; j < kWhole; ++j) {
     float z[16];
     scores(j, z);
     float bm = z[0];
@@ -343,27 +352,19 @@ __global__ __launch_bounds__(NB * 64) void attn_fwd_kernel(const uint16_t* __res
     l = rescaled(mn) + t;
     m = mn;
   }
-  {  // the last block: groups past T skipped, -inf past T in the others
+  if constexpr (LAST != 0) {  // the last block: -inf past T
     float z[16];
     scores(NB - 1, z);
     float bm = -INFINITY;
 #pragma unroll
-    for (int gq = 0; gq < 4; ++gq) {
-      if (!group_in(NB - 1, gq, T)) continue;
-#pragma unroll
-      for (int e = 4 * gq; e < 4 * gq + 4; ++e) {
-        if (key_of(NB - 1, e, hi) >= T) z[e] = -INFINITY;
-        bm = fmaxf(bm, z[e]);
-      }
+    for (int e = 0; e < 4 * kGroups; ++e) {
+      if (key_of(NB - 1, e, hi) >= T) z[e] = -INFINITY;
+      bm = fmaxf(bm, z[e]);
     }
     const float mn = fmaxf(m, bm), mb = base(mn);
     float t = 0.0f;
 #pragma unroll
-    for (int gq = 0; gq < 4; ++gq) {
-      if (!group_in(NB - 1, gq, T)) continue;
-#pragma unroll
-      for (int e = 4 * gq; e < 4 * gq + 4; ++e) t += exp_scaled(z[e] - mb, c2);
-    }
+    for (int e = 0; e < 4 * kGroups; ++e) t += exp_scaled(z[e] - mb, c2);
     l = rescaled(mn) + t;
     m = mn;
   }
@@ -389,7 +390,8 @@ __global__ __launch_bounds__(NB * 64) void attn_fwd_kernel(const uint16_t* __res
     for (int db = 0; db < 2; ++db)
       o[db] = mfma32<DT>(frag_tr(vbase, PD, 32 * j + 16 * hh, 32 * db, lane), bf, o[db]);
   };
-  for (int j = 0; j < NB - 1; ++j) {
+#pragma unroll 2
+  for (int j = 0; j < kWhole; ++j) {
     float z[16];
     scores(j, z);
     u32x2 R4[4];
@@ -402,14 +404,14 @@ __global__ __launch_bounds__(NB * 64) void attn_fwd_kernel(const uint16_t* __res
     keys16(j, 0, R4);
     keys16(j, 1, R4);
   }
-  {
+  if constexpr (LAST != 0) {
     float z[16];
     scores(NB - 1, z);
     u32x2 R4[4];
 #pragma unroll
     for (int gq = 0; gq < 4; ++gq) {
       R4[gq] = u32x2{0u, 0u};
-      if (!group_in(NB - 1, gq, T)) continue;
+      if (gq >= kGroups) continue;
       float ex[4];
 #pragma unroll
       for (int c = 0; c < 4; ++c) {
@@ -419,7 +421,7 @@ __global__ __launch_bounds__(NB * 64) void attn_fwd_kernel(const uint16_t* __res
       R4[gq] = u32x2{pack2<DT>(ex[0], ex[1]), pack2<DT>(ex[2], ex[3])};
     }
     keys16(NB - 1, 0, R4);
-    if (group_in(NB - 1, 2, T)) keys16(NB - 1, 1, R4);
+    if (LAST == 32) keys16(NB - 1, 1, R4);
   }
   if (q < T) {
     uint16_t* out = O + ((int64_t)b * T + q) * dm + h * HD;
@@ -851,8 +853,12 @@ hipError_t launch_fwd(const uint16_t* qkv, uint16_t* O, uint16_t* P, int B, int 
                       float scale, hipStream_t s) {
   const dim3 grid((unsigned)(B * H));
   const int nb = (T + 31) / 32;
-#define MPX_F(NBv) attn_fwd_kernel<DT, NBv><<<grid, NBv * 64, 0, s>>>(qkv, O, P, T, H, ldP, scale)
-#define MPX_FR(NBv) attn_fwd_rows_kernel<DT, NBv><<<grid, NBv * 64, 0, s>>>(qkv, O, P, T, H, ldP, scale)
+#define MPX_FT(KERNEL, NBv)                                                                               \
+  if (T % 32 == 0) KERNEL<DT, NBv, 0><<<grid, NBv * 64, 0, s>>>(qkv, O, P, T, H, ldP, scale);             \
+  else if (T % 32 <= 16) KERNEL<DT, NBv, 16><<<grid, NBv * 64, 0, s>>>(qkv, O, P, T, H, ldP, scale);      \
+  else KERNEL<DT, NBv, 32><<<grid, NBv * 64, 0, s>>>(qkv, O, P, T, H, ldP, scale)
+#define MPX_F(NBv) MPX_FT(attn_fwd_kernel, NBv)
+#define MPX_FR(NBv) MPX_FT(attn_fwd_rows_kernel, NBv)
   switch (nb) {
     case 1: MPX_FR(1); break;
     case 2: MPX_FR(2); break;
@@ -865,6 +871,7 @@ hipError_t launch_fwd(const uint16_t* qkv, uint16_t* O, uint16_t* P, int B, int 
   }
 #undef MPX_FR
 #undef MPX_F
+#undef MPX_FT
   return hipGetLastError();
 }
 
