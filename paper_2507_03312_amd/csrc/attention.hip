@@ -441,14 +441,19 @@ __global__ __launch_bounds__(NB * 64) void attn_fwd_kernel(const uint16_t* __res
 // >= T and so are the probabilities: the sums and products need no masks (a
 // masked term is an exact 0, and dS there is a zero of either sign).
 // Conversions go two values at a time.
-template <int DT, int NB>
+// GROUPS: groups of 8 keys of the last block worked on (4 or 2 at compile time), or
+// 0: those below T (a uniform branch each).
+template <int DT, int NB, int GROUPS = 0>
 __device__ __forceinline__ void probs_to_ds_zero_padded(f32x16 (&dp)[NB], const u32x2 (&Pr)[NB][4],
                                                         float scale, int T, u32x2 (&Sr)[NB][4]) {
+  auto group_past = [&](int j, int gq) {
+    return j == NB - 1 && (GROUPS ? gq >= GROUPS : !group_in(j, gq, T));
+  };
   float rs = 0.0f;
   static_for<NB>([&](auto j) {
 #pragma unroll
     for (int gq = 0; gq < 4; ++gq) {
-      if (j == NB - 1 && !group_in(j, gq, T)) continue;
+      if (group_past(j, gq)) continue;
       float p[4], d[4];
       unpack2<DT>(Pr[j][gq].x, p[0], p[1]);
       unpack2<DT>(Pr[j][gq].y, p[2], p[3]);
@@ -465,7 +470,7 @@ __device__ __forceinline__ void probs_to_ds_zero_padded(f32x16 (&dp)[NB], const 
   static_for<NB>([&](auto j) {
 #pragma unroll
     for (int gq = 0; gq < 4; ++gq) {
-      if (j == NB - 1 && !group_in(j, gq, T)) {
+      if (group_past(j, gq)) {
         Sr[j][gq] = u32x2{0u, 0u};
         continue;
       }
@@ -481,7 +486,7 @@ __device__ __forceinline__ void probs_to_ds_zero_padded(f32x16 (&dp)[NB], const 
 
 // dQ^T = K^T dS^T for the wave's queries (K staged in LDS as [key][d]):
 // the float32 accumulators (lane = query, d in registers).
-template <int DT, int NB>
+template <int DT, int NB, int GROUPS = 0>
 __device__ __forceinline__ void bwd_dq_acc(uint32_t kbase, const u32x2 (&Sr)[NB][4], int T, int lane,
                                            f32x16 (&o)[2]) {
 #pragma unroll
@@ -489,7 +494,7 @@ __device__ __forceinline__ void bwd_dq_acc(uint32_t kbase, const u32x2 (&Sr)[NB]
 #pragma unroll
     for (int e = 0; e < 16; ++e) o[db][e] = 0.0f;
   static_for<2 * NB>([&](auto ks) {
-    if (ks == 2 * NB - 1 && 16 * ks >= T) return;  // no key (uniform)
+    if (ks == 2 * NB - 1 && (GROUPS ? GROUPS == 2 : 16 * ks >= T)) return;  // no key (uniform)
     const uint4 bf = keys_operand<NB>(Sr, ks);
 #pragma unroll
     for (int db = 0; db < 2; ++db) o[db] = mfma32<DT>(frag_tr(kbase, PD, 16 * ks, 32 * db, lane), bf, o[db]);
@@ -504,11 +509,11 @@ __device__ __forceinline__ void put_dq_row(const f32x16 (&o)[2], uint16_t* row, 
 }
 
 // dQ for the wave's queries, stored for queries < T.
-template <int DT, int NB>
+template <int DT, int NB, int GROUPS = 0>
 __device__ __forceinline__ void bwd_dq(uint32_t kbase, const u32x2 (&Sr)[NB][4], uint16_t* dQrow, int q,
                                        int T, int lane) {
   f32x16 o[2];
-  bwd_dq_acc<DT, NB>(kbase, Sr, T, lane, o);
+  bwd_dq_acc<DT, NB, GROUPS>(kbase, Sr, T, lane, o);
   if (q < T) put_dq_row<DT>(o, dQrow, lane);
 }
 
@@ -542,7 +547,7 @@ __device__ __forceinline__ void store_kv_block(const f32x16 (&dk)[2], const f32x
 // masked to 0, so dP is 0 there and dS needs no masks
 // (probs_to_ds_zero_padded).  The masks are ANDs, not selects: a select lets
 // the compiler turn the load into a branch around it.
-template <int DT, int NB>
+template <int DT, int NB, int GROUPS>
 __device__ __forceinline__ void bwd_query_block_zp(const uint16_t* V, int64_t ld, const uint16_t* G, int dm,
                                                    const uint16_t* Pbh, int ldP, int q, int T, float scale,
                                                    int lane, u32x2 (&Pr)[NB][4], u32x2 (&Sr)[NB][4]) {
@@ -580,37 +585,51 @@ __device__ __forceinline__ void bwd_query_block_zp(const uint16_t* V, int64_t ld
     }
     dp[j] = acc;
   });
-  probs_to_ds_zero_padded<DT, NB>(dp, Pr, scale, T, Sr);
+  probs_to_ds_zero_padded<DT, NB, GROUPS>(dp, Pr, scale, T, Sr);
+}
+
+// LDS of the short backward (T <= 128), in bytes: R rows of Q and dO, and K
+// beside the [query][key] arrays P and dS, or (SHARE) in their place before
+// they are written.  The arrays' pitch in halves is R + 8: 4 consecutive rows of a
+// transposed read land in distinct banks.  The last key block's reads may run
+// past a row's end (keys >= T, whose results are not stored): into the next
+// row, or behind the last row into the slack of 32 halves.
+constexpr int bwd_pds_halves(int R) { return 2 * R * (R + 8) + 32; }
+constexpr int bwd_kps_halves(int R, bool share) {
+  return !share ? R * PD + bwd_pds_halves(R) : R * PD > bwd_pds_halves(R) ? R * PD : bwd_pds_halves(R);
+}
+constexpr int bwd_lds(int R, bool share) { return 2 * (2 * R * PD + bwd_kps_halves(R, share)); }
+// workgroups of one wave per 32 rows that LDS lets a CU hold
+constexpr int bwd_per_cu(int R, bool share) { return 160 * 1024 / bwd_lds(R, share); }
+// waves per SIMD (of 4) that those workgroups need, at most 3: the registers of
+// the short forms already allow 4
+constexpr int bwd_waves(int R, bool share) {
+  const int w = (bwd_per_cu(R, share) * ((R + 31) / 32) + 3) / 4;
+  return w < 3 ? w : 3;
 }
 
 // T <= 128: the whole backward of one (batch, head) in one workgroup.  R: T
 // rounded up to 16, the rows kept in LDS.  What bounds it is latency: a
 // workgroup loads, multiplies and stores in turn, so the workgroups a CU
-// holds overlap those phases, and LDS decides how many it holds.  The P and dS
-// arrays therefore take K's place once dQ is done, and R rows are kept instead
-// of whole blocks of 32: 51 KB at 65 tokens (3 workgroups per CU) where
-// separate arrays of 96 rows took 81 KB (2).
-template <int DT, int R>
+// holds overlap those phases, and LDS decides how many it holds.  SHARE: the P
+// and dS arrays take K's place once dQ is done, at the price of one more barrier:
+// 51 KB at 65 tokens (3 workgroups per CU) where separate arrays take 63 KB (2).
+template <int DT, int R, bool SHARE>
 __global__ __launch_bounds__((R + 31) / 32 * 64)
-// 9 waves per CU at R = 80: one SIMD holds three
-__attribute__((amdgpu_waves_per_eu(R == 80 ? 3 : 1)))
+__attribute__((amdgpu_waves_per_eu(bwd_waves(R, SHARE))))
 void attn_bwd_kernel(const uint16_t* __restrict__ qkv,
                                                            const uint16_t* __restrict__ P,
                                                            const uint16_t* __restrict__ dO,
                                                            uint16_t* __restrict__ dqkv, int T, int H,
                                                            int ldP, float scale) {
   constexpr int NB = (R + 31) / 32;
-  // pitch (halves) of the [query][key] arrays: 4 consecutive rows of a
-  // transposed read land in distinct banks.  The last key block's reads may
-  // run past a row's end (keys >= T, whose results are not stored): into the
-  // next row, or behind the last row into the slack of 32 halves
+  constexpr int kGroups = R % 32 == 16 ? 2 : 4;  // groups of 8 keys of the last block
   constexpr int PK = R + 8;
-  constexpr int KPS = R * PD > 2 * R * PK + 32 ? R * PD : 2 * R * PK + 32;
   __shared__ __attribute__((aligned(16))) uint16_t sQ[R * PD];
   __shared__ __attribute__((aligned(16))) uint16_t sdO[R * PD];
-  __shared__ __attribute__((aligned(16))) uint16_t sK[KPS];  // K, then P and dS
-  uint16_t* sP = sK;
-  uint16_t* sdS = sK + R * PK;
+  __shared__ __attribute__((aligned(16))) uint16_t sK[bwd_kps_halves(R, SHARE)];  // K and P, dS
+  uint16_t* sP = SHARE ? sK : sK + R * PD;
+  uint16_t* sdS = sP + R * PK;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int bh = blockIdx.x, b = bh / H, h = bh % H;
   const int dm = H * HD;
@@ -633,13 +652,10 @@ void attn_bwd_kernel(const uint16_t* __restrict__ qkv,
 
   const int q = 32 * w + (lane & 31);
   u32x2 Pr[NB][4], Sr[NB][4];
-  bwd_query_block_zp<DT, NB>(V, ld, G, dm, P + (int64_t)bh * T * ldP, ldP, q, T, scale, lane, Pr, Sr);
-  __syncthreads();  // sK / sQ / sdO staged
-
-  bwd_dq<DT, NB>(lds_u32(sK), Sr, dQ + q * ld, q, T, lane);
-  __syncthreads();  // sK is read
+  bwd_query_block_zp<DT, NB, kGroups>(V, ld, G, dm, P + (int64_t)bh * T * ldP, ldP, q, T, scale, lane, Pr, Sr);
   // the [query][key] copies for the dK / dV products (rows T..R-1 are 0)
-  if (q < R) {
+  auto put = [&] {
+    if (q >= R) return;
     static_for<NB>([&](auto j) {
 #pragma unroll
       for (int gq = 0; gq < 4; ++gq) {
@@ -649,8 +665,16 @@ void attn_bwd_kernel(const uint16_t* __restrict__ qkv,
         *reinterpret_cast<u32x2*>(sdS + q * PK + key0) = Sr[j][gq];
       }
     });
+  };
+  if constexpr (!SHARE) put();
+  __syncthreads();  // sK / sQ / sdO staged; without SHARE sP / sdS complete
+
+  bwd_dq<DT, NB, kGroups>(lds_u32(sK), Sr, dQ + q * ld, q, T, lane);
+  if constexpr (SHARE) {
+    __syncthreads();  // sK is read
+    put();
+    __syncthreads();  // sP / sdS complete
   }
-  __syncthreads();  // sP / sdS complete
 
   // per key block (wave w): dK = dS^T Q and dV = P^T dO over all queries
   const uint32_t qbase = lds_u32(sQ), gbase = lds_u32(sdO), pbase = lds_u32(sP), sbase = lds_u32(sdS);
@@ -879,7 +903,18 @@ template <int DT>
 hipError_t launch_bwd(const uint16_t* qkv, const uint16_t* P, const uint16_t* dO, uint16_t* dqkv, int B,
                       int T, int H, int ldP, float scale, hipStream_t s) {
   const dim3 grid((unsigned)(B * H));
-#define MPX_B(Rv) attn_bwd_kernel<DT, Rv><<<grid, (Rv + 31) / 32 * 64, 0, s>>>(qkv, P, dO, dqkv, T, H, ldP, scale)
+// P and dS in K's place where that lets a CU hold more workgroups and the grid
+// has them (us, shared / separate: 256 workgroups of 32 tokens 5.2 / 4.9, of 64
+// tokens 7.2 / 6.7, of 96, where two fit either way, 10.5 / 10.0; 1536 workgroups
+// of 65 tokens 25.3 / 29.1, that with 96 rows kept)
+#define MPX_B(Rv)                                                                                            \
+  if constexpr (bwd_per_cu(Rv, true) > bwd_per_cu(Rv, false)) {                                              \
+    if (B * (int64_t)H > 256 * bwd_per_cu(Rv, false)) {                                                      \
+      attn_bwd_kernel<DT, Rv, true><<<grid, (Rv + 31) / 32 * 64, 0, s>>>(qkv, P, dO, dqkv, T, H, ldP, scale); \
+      break;                                                                                                 \
+    }                                                                                                        \
+  }                                                                                                          \
+  attn_bwd_kernel<DT, Rv, false><<<grid, (Rv + 31) / 32 * 64, 0, s>>>(qkv, P, dO, dqkv, T, H, ldP, scale)
 #define MPX_B2(NBv) attn_bwd_fused_kernel<DT, NBv><<<grid, NBv * 64, 0, s>>>(qkv, P, dO, dqkv, T, H, ldP, scale)
   if (T <= 128) {
     switch ((T + 15) / 16) {

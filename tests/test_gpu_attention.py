@@ -201,3 +201,27 @@ def test_overflowed_scores_are_zero_probabilities(T, keys):
     assert np.all(gP[..., keys] == 0.0)
     assert_within(gP[..., :T], P, bP, "P")
     assert np.all(np.isfinite(gO))
+
+
+@pytest.mark.parametrize("bht", [(1300, 4, 9), (400, 6, 20), (220, 7, 40), (200, 4, 50), (130, 4, 65), (50, 6, 81)],
+                         ids=lambda s: "x".join(map(str, s)))
+def test_backward_of_large_grids(bht):
+    """Grids past what the chip holds at a time (up to 80 tokens P and dS then
+    take K's place in LDS): the same bits as the same entries in grids of one."""
+    B, H, T = bht
+    fmt, d, ldP = "bf16", H * HD, -(-T // 8) * 8
+    gen = torch.Generator(device="cuda").manual_seed(T)
+    rnd = lambda *s: torch.randn(*s, generator=gen, device="cuda").to(torch.bfloat16)  # noqa: E731
+    qkv, dout, dt = rnd(B, T, 3 * d), rnd(B, T, d), mx.DTYPES[fmt]
+    O, P, dq = _empty((B, T, d), fmt), _empty((B, H * T, ldP), fmt), _empty((B, T, 3 * d), fmt)
+
+    def run(x, g, o, p, out, n):
+        mx.mpx_attention_fwd(x.data_ptr(), o.data_ptr(), p.data_ptr(), n, T, H, HD, dt, _s())
+        mx.mpx_attention_bwd(x.data_ptr(), p.data_ptr(), g.data_ptr(), out.data_ptr(), n, T, H, HD, dt, None, 0, _s())
+
+    run(qkv, dout, O, P, dq, B)
+    for i in (0, 1, B // 2, B - 1):
+        one = _empty((T, d), fmt), _empty((H * T, ldP), fmt), _empty((T, 3 * d), fmt)
+        run(qkv[i], dout[i], *one, 1)
+        for got, want in zip((O[i], P[i], dq[i]), one):
+            assert torch.equal(got, want)
