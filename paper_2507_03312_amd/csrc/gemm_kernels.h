@@ -56,8 +56,9 @@ struct GemmArgs {
   // weight-gradient products (both operands mn-major) may also return the
   // bias gradient db[m] = half(sum_k A(m, k)), summed from the A fragments
   // the MFMAs read: set by the dispatcher only for the kernel variant that
-  // does it.  Split-K calls write float32 partial sums dbp[split][M] instead,
-  // which the split-K reduction adds in split order.
+  // does it.  Split-K calls write float32 partial sums dbp[M][splits * C] instead,
+  // one per split and column of the output's C tile columns, which the split-K
+  // reduction adds.
   uint16_t* db;
   float* dbp;
 };
@@ -65,10 +66,7 @@ struct GemmArgs {
 // Epilogue operations compiled into a kernel (a mask of these bits);
 // EPI_GENERIC takes them from the call's arguments, the same arithmetic step
 // for step.
-// EPI_COUNT: add the number of non-finite outputs to g.nonfinite (weight
-// gradients, which have no other epilogue operation)
-enum : int { EPI_BIAS = 1, EPI_GELU = 2, EPI_DACT = 4, EPI_RESID = 8, EPI_COUNT = 16,
-             EPI_GENERIC = -1 };
+enum : int { EPI_BIAS = 1, EPI_GELU = 2, EPI_DACT = 4, EPI_RESID = 8, EPI_GENERIC = -1 };
 
 // 16 bytes at any 2-byte aligned address (one instruction: global accesses
 // need no alignment on gfx950)
@@ -104,7 +102,7 @@ __device__ __forceinline__ void gemm_epilogue_lds(const GemmArgs& g, const f32x1
   const bool do_gelu = E == EPI_GENERIC ? g.act == MPX_ACT_GELU_TANH : (E & EPI_GELU) != 0;
   const bool do_dact = E == EPI_GENERIC ? g.dact != nullptr : (E & EPI_DACT) != 0;
   const bool do_res = E == EPI_GENERIC ? g.resid != nullptr : (E & EPI_RESID) != 0;
-  const bool do_count = E == EPI_GENERIC ? g.nonfinite != nullptr : (E & EPI_COUNT) != 0;
+  const bool do_count = E == EPI_GENERIC && g.nonfinite != nullptr;
   auto unpack = [](u32x2 w, float (&f)[4]) {
     f[0] = h2f<DT>((uint16_t)(w.x & 0xFFFFu));
     f[1] = h2f<DT>((uint16_t)(w.x >> 16));
@@ -846,9 +844,11 @@ static bool aligned_vec(const void* p, int64_t ld, int64_t s0, int64_t s1) {
   return (reinterpret_cast<uintptr_t>(p) & 15u) == 0 && ld % 8 == 0 && s0 % 8 == 0 && s1 % 8 == 0;
 }
 
-// Epilogue mask of a call, or EPI_GENERIC when it has no compiled variant
+// Epilogue mask of a call: 0 with split-K, whose kernels end before it, and
+// EPI_GENERIC for calls that count non-finite outputs (weight gradients).
 static int epilogue_mask(const GemmArgs& g) {
-  if (g.splits > 1) return EPI_GENERIC;
+  if (g.splits > 1) return 0;
+  if (g.nonfinite) return EPI_GENERIC;
   return (g.bias ? EPI_BIAS : 0) | (g.act == MPX_ACT_GELU_TANH ? EPI_GELU : 0) |
          (g.dact ? EPI_DACT : 0) | (g.resid ? EPI_RESID : 0);
 }
@@ -867,6 +867,44 @@ static bool full_epilogue_ok(const GemmArgs& g, int bm) {
          g.ldr * bm < ((int64_t)1 << 30);
 }
 
+// The kernel of a call's layouts and epilogue: the epilogues of the library's own
+// calls are compiled in, any other takes the generic one, which loads its
+// operand row by row between the stores and is several times the code (forward
+// with residual 8366 x 856 x 104 bf16 generic / compiled in 23.6 / 16.4 us, 395
+// products of 128 x 128 x 128 11.2 / 10.4).  MPX_K(AK, BKM, E, DBS) launches.
+#define MPX_BY_EPILOGUE(ALL_LAYOUTS)                                         \
+  do {                                                                       \
+    const int e = epilogue_mask(g);                                          \
+    if (ak && bk) {                                                          \
+      switch (e) {                                                           \
+        case 0: MPX_K(true, true, 0, false); break;                          \
+        case EPI_BIAS: MPX_K(true, true, EPI_BIAS, false); break;            \
+        case EPI_BIAS | EPI_GELU: MPX_K(true, true, EPI_BIAS | EPI_GELU, false); break;   \
+        case EPI_BIAS | EPI_RESID: MPX_K(true, true, EPI_BIAS | EPI_RESID, false); break; \
+        default: MPX_K(true, true, EPI_GENERIC, false);                      \
+      }                                                                      \
+    } else if (ak) {                                                         \
+      switch (e) {                                                           \
+        case 0: MPX_K(true, false, 0, false); break;                         \
+        case EPI_DACT: MPX_K(true, false, EPI_DACT, false); break;           \
+        default: MPX_K(true, false, EPI_GENERIC, false);                     \
+      }                                                                      \
+    } else if constexpr (ALL_LAYOUTS) {                                      \
+      if (bk) {                                                              \
+        if (e == 0) MPX_K(false, true, 0, false);                            \
+        else MPX_K(false, true, EPI_GENERIC, false);                         \
+      } else if (g.db) { /* weight gradient, the bias gradient summed alongside */ \
+        if (e == 0) MPX_K(false, false, 0, true);                            \
+        else MPX_K(false, false, EPI_GENERIC, true);                         \
+      } else {                                                               \
+        if (e == 0) MPX_K(false, false, 0, false);                           \
+        else MPX_K(false, false, EPI_GENERIC, false);                        \
+      }                                                                      \
+    } else {                                                                 \
+      return hipErrorInvalidValue;                                           \
+    }                                                                        \
+  } while (0)
+
 // Direct-to-LDS tiles.  The 128 x 128 ones take every layout; the others a
 // k-major A (forward, dX) without split-K.
 template <int DT, int BM, int BN, int WM, int WN, int OCC>
@@ -875,34 +913,10 @@ hipError_t launch_tiles(GemmArgs g, bool ak, bool bk, int64_t nbatch, hipStream_
   const int64_t tiles = ((g.M + BM - 1) / BM) * ((g.N + BN - 1) / BN);
   dim3 grid((unsigned)tiles, (unsigned)(g.splits > 1 ? g.splits : nbatch));
   g.full_epi = full_epilogue_ok(g, BM) ? 1 : 0;
-  const int e = epilogue_mask(g) | (g.nonfinite ? EPI_COUNT : 0);
-#define MPX_T(AKv, BKv, Ev, DBv) \
+#define MPX_K(AKv, BKv, Ev, DBv) \
   gemm_tile_kernel<DT, BM, BN, WM, WN, OCC, AKv, BKv, Ev, DBv><<<grid, NT, 0, s>>>(g)
-  if (ak && bk) {
-    switch (e) {
-      case EPI_BIAS: MPX_T(true, true, EPI_BIAS, false); break;
-      case EPI_BIAS | EPI_GELU: MPX_T(true, true, EPI_BIAS | EPI_GELU, false); break;
-      case EPI_BIAS | EPI_RESID: MPX_T(true, true, EPI_BIAS | EPI_RESID, false); break;
-      default: MPX_T(true, true, EPI_GENERIC, false);
-    }
-  } else if (ak) {
-    switch (e) {
-      case 0: MPX_T(true, false, 0, false); break;
-      case EPI_DACT: MPX_T(true, false, EPI_DACT, false); break;
-      default: MPX_T(true, false, EPI_GENERIC, false);
-    }
-  } else if constexpr (BM == 128 && BN == 128) {
-    if (bk) {
-      MPX_T(false, true, EPI_GENERIC, false);
-    } else if (g.db) {  // weight gradient with the bias gradient summed alongside
-      MPX_T(false, false, EPI_GENERIC, true);
-    } else {
-      MPX_T(false, false, EPI_GENERIC, false);
-    }
-  } else {
-    return hipErrorInvalidValue;
-  }
-#undef MPX_T
+  MPX_BY_EPILOGUE((BM == 128 && BN == 128));
+#undef MPX_K
   return hipGetLastError();
 }
 
@@ -913,36 +927,18 @@ inline bool staged_any(const GemmArgs& g, bool ak, bool bk) {
   return (ak ? g.K : g.M) < 8 || (bk ? g.K : g.N) < 8 || g.lda * 256 >= lim || g.ldb * 256 >= lim;
 }
 
-// Operands staged through registers: any alignment, any reduction length
-// (128 x 128 tiles: not for operands of staged_any).
-template <int DT, int BM, int BN, int WM, int WN>
+// Operands staged through registers (STG 1: any alignment, any reduction
+// length; 2: those of staged_any).
+template <int DT, int BM, int BN, int WM, int WN, int STG>
 hipError_t launch_staged(GemmArgs g, bool ak, bool bk, int64_t nbatch, hipStream_t s) {
   constexpr int NT = (BM / WM) * (BN / WN) * 64;
   const int64_t tiles = ((g.M + BM - 1) / BM) * ((g.N + BN - 1) / BN);
   dim3 grid((unsigned)tiles, (unsigned)(g.splits > 1 ? g.splits : nbatch));
   g.full_epi = full_epilogue_ok(g, BM) ? 1 : 0;
-#define MPX_S(AKv, BKv, Ev, DBv, STGv) \
-  gemm_tile_kernel<DT, BM, BN, WM, WN, 2, AKv, BKv, Ev, DBv, STGv><<<grid, NT, 0, s>>>(g)
-#define MPX_S_LAYOUTS(STGv)                                       \
-  do {                                                            \
-    if (ak && bk) MPX_S(true, true, EPI_GENERIC, false, STGv);    \
-    else if (ak) MPX_S(true, false, EPI_GENERIC, false, STGv);    \
-    else if (bk) MPX_S(false, true, EPI_GENERIC, false, STGv);    \
-    else if (g.db) MPX_S(false, false, EPI_GENERIC, true, STGv);  \
-    else MPX_S(false, false, EPI_GENERIC, false, STGv);           \
-  } while (0)
-  if constexpr (BM == 128) {  // the forward's epilogues compiled in
-    const int e = epilogue_mask(g);
-    if (ak && bk && e == EPI_BIAS) MPX_S(true, true, EPI_BIAS, false, 1);
-    else if (ak && bk && e == (EPI_BIAS | EPI_GELU)) MPX_S(true, true, EPI_BIAS | EPI_GELU, false, 1);
-    else MPX_S_LAYOUTS(1);
-  } else if (staged_any(g, ak, bk)) {
-    MPX_S_LAYOUTS(2);
-  } else {
-    MPX_S_LAYOUTS(1);
-  }
-#undef MPX_S_LAYOUTS
-#undef MPX_S
+#define MPX_K(AKv, BKv, Ev, DBv) \
+  gemm_tile_kernel<DT, BM, BN, WM, WN, 2, AKv, BKv, Ev, DBv, STG><<<grid, NT, 0, s>>>(g)
+  MPX_BY_EPILOGUE(true);
+#undef MPX_K
   return hipGetLastError();
 }
 
@@ -951,8 +947,9 @@ hipError_t launch_staged(GemmArgs g, bool ak, bool bk, int64_t nbatch, hipStream
 // (gemm_wide_f16.hip) and the register-staged ones (gemm_staged_f16.hip);
 // likewise for bf16.
 #define MPX_GEMM_STAGED(X, DT)                                                              \
-  X template hipError_t launch_staged<DT, 64, 64, 32, 32>(GemmArgs, bool, bool, int64_t, hipStream_t); \
-  X template hipError_t launch_staged<DT, 128, 128, 64, 64>(GemmArgs, bool, bool, int64_t, hipStream_t);
+  X template hipError_t launch_staged<DT, 64, 64, 32, 32, 1>(GemmArgs, bool, bool, int64_t, hipStream_t); \
+  X template hipError_t launch_staged<DT, 64, 64, 32, 32, 2>(GemmArgs, bool, bool, int64_t, hipStream_t); \
+  X template hipError_t launch_staged<DT, 128, 128, 64, 64, 1>(GemmArgs, bool, bool, int64_t, hipStream_t);
 #define MPX_GEMM_WIDE(X, DT)                                                                \
   X template hipError_t launch_tiles<DT, 256, 256, 128, 64, 2>(GemmArgs, bool, bool, int64_t, hipStream_t); \
   X template hipError_t launch_tiles<DT, 128, 192, 64, 96, 2>(GemmArgs, bool, bool, int64_t, hipStream_t);
@@ -1127,8 +1124,10 @@ static hipError_t run_gemm(GemmArgs g, bool ak, bool bk, int64_t nbatch, hipStre
   }
   switch (cfg) {
     case 8: return launch_small<DT>(g, ak, bk, s);
-    case 1: return launch_staged<DT, 64, 64, 32, 32>(g, ak, bk, nbatch, s);
-    case 2: return launch_staged<DT, 128, 128, 64, 64>(g, ak, bk, nbatch, s);
+    case 1:
+      return staged_any(g, ak, bk) ? launch_staged<DT, 64, 64, 32, 32, 2>(g, ak, bk, nbatch, s)
+                                   : launch_staged<DT, 64, 64, 32, 32, 1>(g, ak, bk, nbatch, s);
+    case 2: return launch_staged<DT, 128, 128, 64, 64, 1>(g, ak, bk, nbatch, s);
     case 3: return launch_tiles<DT, 256, 256, 128, 64, 2>(g, ak, bk, nbatch, s);
     case 5: return launch_tiles<DT, 128, 192, 64, 96, 2>(g, ak, bk, nbatch, s);
     case 7: return launch_tiles<DT, 128, 128, 64, 64, 2>(g, ak, bk, nbatch, s);
