@@ -1038,15 +1038,21 @@ static int choose_config(const GemmArgs& g, bool vec, bool ak, bool bk, int64_t 
   const bool any = staged_any(g, ak, bk);
   if (f == 1 || f == 2) return any ? 1 : f;
   if (small && (g.M <= 32 || g.N <= 32 || g.K <= 32)) return 8;
-  // 64 x 64 register-staged tiles: outputs of up to 64 columns, and products
-  // the tiles of choose_tiles do not take whose 64 x 64 tiles fit one per CU
-  // (us, 64 x 64 against 128 x 128: forward 256 x 100 x 384 6.4 / 8.9, dX
-  // there 4.3 / 6.3, 300 x 300 x 300 7.5 / 10.2, dW of 1000 rows 768 x 768
-  // 10.7 / 21.8, dW of 256 rows 1024 x 512 6.0 / 7.3; at 3001 x 515 x 301, 423
-  // tiles, still 9.4 / 11.7 forward, at 8415 x 768 x 588 31 / 22)
+  // 64 x 64 register-staged tiles (us, against the tile that would be taken
+  // otherwise):
+  // - outputs of up to 64 columns or rows: forward 43 x 192 x 64 5.0 / 6.5 with
+  //   64 x 128 tiles, 256 x 100 x 384 6.4 / 8.9 and dX there 4.3 / 6.3 with 128 x 128, a
+  //   split dW of 64 x 128 over 3310 rows 17 / 24.  Not dX of up to 64 rows on the direct
+  //   tiles (equal up to K = 1024; the staged ones gain 8% only beyond).
+  // - products the tiles of choose_tiles do not take, with so few 64 x 64 tiles
+  //   that smaller ones spread the work: up to two per CU against the staged
+  //   128 x 128 tiles (1000 x 768 x 768 dW, unaligned, 0.6 of their time; at 768 tiles
+  //   1.1), one per CU against the direct ones (dW and batched products of 256 tiles
+  //   0.86 to 1.03, of 512 1.04 to 1.6)
   const int64_t t64 = ((g.M + 63) / 64) * ((g.N + 63) / 64) * nbatch;
   const bool tiles = dma && ak && g.splits == 1;
-  if (any || g.N <= 64 || (!tiles && g.splits == 1 && (g.M <= 64 || t64 <= 512))) return 1;
+  if (any || g.N <= 64 || (g.M <= 64 && (bk || !tiles))) return 1;
+  if (!tiles && g.splits == 1 && t64 <= (dma ? 256 : 512)) return 1;
   if (tiles) return choose_tiles(g, nbatch);
   return dma ? 7 : 2;
 }
