@@ -109,6 +109,7 @@ __device__ __forceinline__ void gemm_epilogue_lds(const GemmArgs& g, const f32x1
     f[2] = h2f<DT>((uint16_t)(w.y & 0xFFFFu));
     f[3] = h2f<DT>((uint16_t)(w.y >> 16));
   };
+  asm volatile("" ::: "memory");  // the wave's reads of its last 64 columns come first
   static_for<TN>([&](auto j) {
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
@@ -188,6 +189,7 @@ __device__ __forceinline__ void gemm_epilogue_lds(const GemmArgs& g, const f32x1
       else op[t] = u32x4{0u, 0u, 0u, 0u};
     }
   }
+  asm volatile("" ::: "memory");  // the lanes' writes to LDS come before the wave's reads
   auto operand8 = [&](int t, const uint16_t* p, uint16_t (&h)[8]) {
     if (kOp && nc == 8) h8(op[kOp ? t : 0], h);
     else load8(p, h);
