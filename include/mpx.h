@@ -189,8 +189,9 @@ int mpx_linear_fwd(const void* X, const void* W, const void* b, const void* R, v
  * `workspace` (device, ws_bytes) holds split-K partial sums and column
  * partials; its required size is mpx_linear_bwd_workspace(M, N, K) when dW
  * or db is requested (a dX-only call needs none, a db-only call only the
- * column partials, which that size always covers).  Concurrent calls need
- * separate workspaces.  d_nonfinite (nullable) counts non-finite dW and db
+ * column partials, which that size always covers); it never falls as M grows,
+ * so a workspace for the largest batch serves smaller ones.  Concurrent calls
+ * need separate workspaces.  d_nonfinite (nullable) counts non-finite dW and db
  * elements (MPX §3.4's check, fused into the kernels that write them).
  * dt == MPX_F32: the same products in float32 (full precision, see
  * mpx_linear_fwd; the workspace size is the same); d_nonfinite must be NULL. */
@@ -214,7 +215,7 @@ size_t mpx_linear_bwd_workspace(int64_t M, int64_t N, int64_t K);
  * output tiles of 128 x 128 float32 sums); the column partials of db take
  * 4 bytes per output column per row slice, so only layers with more than
  * about 16 million outputs are rejected (every weight gradient of the ViT
- * workloads needs at most about 28 MB).  All calls on one GPU share its array: calls that overlap on that
+ * workloads needs at most about 31 MB).  All calls on one GPU share its array: calls that overlap on that
  * GPU (concurrent streams, or host threads) race and give wrong results;
  * order them on one stream or with events.  The first call on a GPU looks up
  * the array's device address (hipGetSymbolAddress, not a stream operation);

@@ -26,6 +26,14 @@ static GemmArgs base_args() {
   return g;
 }
 
+// The most splits choose_splits considers for a reduction of length K over an
+// M x N output.  It never falls as K grows, where the chosen count may (2304 x 768:
+// 4 for 7936 rows, 2 for 7952, 4 again for 12608).
+static int64_t most_splits(int64_t M, int64_t N, int64_t K) {
+  const int64_t tiles = ((M + 127) / 128) * ((N + 127) / 128);
+  return std::max<int64_t>(1, std::min<int64_t>({512 / tiles, 16, K / 1024}));
+}
+
 // split-K plan for a reduction of length K over an MxN output (the weight
 // gradients, whose outputs have far fewer 128 x 128 tiles than the chip has
 // workgroup slots): the split count of least estimated time, with at most 512
@@ -42,10 +50,10 @@ static GemmArgs base_args() {
 // ViT-B step, where these run beside the critical path, 10.98 -> 10.55 ms.
 static int choose_splits(int64_t M, int64_t N, int64_t K) {
   const int64_t tiles = ((M + 127) / 128) * ((N + 127) / 128);
-  const int64_t most = std::min<int64_t>({512 / tiles, 16, K / 1024});
+  const int64_t most = most_splits(M, N, K);
   int best = 1;
   double least = 0.0;
-  for (int64_t s = 1; s <= std::max<int64_t>(most, 1); ++s) {
+  for (int64_t s = 1; s <= most; ++s) {
     // k tiles x their time in the full rounds and in the last one
     const int64_t wgs = tiles * s, full = wgs / 512, last = (wgs % 512 + 255) / 256;
     const double k_tile = 1.07 * (double)full + (last == 2 ? 1.07 : last == 1 ? 0.74 : 0.0);
@@ -131,7 +139,9 @@ static size_t db_partials_count(int splits, int64_t N, int64_t K) {
 
 extern "C" size_t mpx_linear_bwd_workspace(int64_t M, int64_t N, int64_t K) {
   if (M < 1 || N < 1 || K < 1) return 0;
-  const int s = choose_splits(N, K, M);
+  // sized for the most splits any M up to this one may take: a workspace for the
+  // largest batch serves every smaller one
+  const int s = (int)most_splits(N, K, M);
   size_t ws = s > 1 ? db_partials_offset(s, N, K) + db_partials_count(s, N, K) * sizeof(float) : 0;
   return std::max(ws, colsum_workspace(M, N)) + 256;
 }

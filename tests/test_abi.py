@@ -46,6 +46,16 @@ def test_binding_loads_and_covers_the_header():
 
 
 @pytest.mark.skipif(not os.path.exists(LIB), reason="libmpx.so not built")
+@pytest.mark.parametrize("nk", [(2304, 768), (1152, 384), (1000, 768), (64, 64), (640, 1216)],
+                         ids=lambda s: "x".join(map(str, s)))
+def test_linear_bwd_workspace_never_falls_with_the_batch(nk):
+    """A workspace sized for the largest batch is accepted for every smaller one."""
+    from paper_2507_03312_amd import binding as mx
+    sizes = [mx.mpx_linear_bwd_workspace(M, *nk) for M in range(1, 40001, 13)]
+    assert sizes == sorted(sizes)
+
+
+@pytest.mark.skipif(not os.path.exists(LIB), reason="libmpx.so not built")
 def test_argument_checks_of_the_float32_and_fused_paths():
     """Host-side argument checks return an error before anything is
     dereferenced or launched (the pointers here are placeholders)."""
