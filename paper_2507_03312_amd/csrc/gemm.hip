@@ -34,11 +34,23 @@ static int64_t most_splits(int64_t M, int64_t N, int64_t K) {
   return std::max<int64_t>(1, std::min<int64_t>({512 / tiles, 16, K / 1024}));
 }
 
+// Cost of a k tile of 64 (us) with one and with two workgroups per CU.
+// Float32: the direct kernel is bound by the matrix cores, so a second workgroup
+// costs nearly a second time; the register-staged one waits for its loads with one
+// workgroup and is slower altogether.  With the half kernel's figures 2276 x 1728
+// over 3174 rows (staged) ran unsplit, 487 us against 319 in 2 splits, and 2298 x
+// 220 over 16955 in 7 splits, 382 against 265 in 14.
+struct SplitCost {
+  double one, two;
+};
+static constexpr SplitCost kHalfCost = {0.74, 1.07};
+static constexpr SplitCost kF32DirectCost = {4.5, 8.0}, kF32StagedCost = {9.7, 13.5};
+
 // split-K plan for a reduction of length K over an MxN output (the weight
 // gradients, whose outputs have far fewer 128 x 128 tiles than the chip has
 // workgroup slots): the split count of least estimated time, with at most 512
 // workgroups (two per CU), 16 splits and at least 1024 reduction values each.
-// A k tile of 64 takes 0.74 us with one workgroup per CU and 1.07 us with two
+// A k tile of 64 takes c.one with one workgroup per CU and c.two with two
 // (256 + 1 workgroups cost as much as 512; a third round as much again), and
 // each split's float32 partials cost their write and read, 8 bytes per output:
 // 1.8 us per million outputs alone, charged as 3.5 because the partials also
@@ -48,7 +60,10 @@ static int64_t most_splits(int64_t M, int64_t N, int64_t K) {
 // rounded up, the rule before: 12608 x 2304 x 768 3 -> 4 splits 82 -> 69 us,
 // 12608 x 3072 x 768 2 -> 3 splits 93 -> 78 us with operands from HBM; the
 // ViT-B step, where these run beside the critical path, 10.98 -> 10.55 ms.
-static int choose_splits(int64_t M, int64_t N, int64_t K) {
+// 90 drawn bf16 gradients (2048 to 40000 rows, 32 to 3072 outputs a side) with
+// every count timed alone: 0.7% slower on average than the fastest count, 0.2%
+// with a charge of 1.8.
+static int choose_splits(int64_t M, int64_t N, int64_t K, SplitCost c) {
   const int64_t tiles = ((M + 127) / 128) * ((N + 127) / 128);
   const int64_t most = most_splits(M, N, K);
   int best = 1;
@@ -56,7 +71,7 @@ static int choose_splits(int64_t M, int64_t N, int64_t K) {
   for (int64_t s = 1; s <= most; ++s) {
     // k tiles x their time in the full rounds and in the last one
     const int64_t wgs = tiles * s, full = wgs / 512, last = (wgs % 512 + 255) / 256;
-    const double k_tile = 1.07 * (double)full + (last == 2 ? 1.07 : last == 1 ? 0.74 : 0.0);
+    const double k_tile = c.two * (double)full + (last == 2 ? c.two : last == 1 ? c.one : 0.0);
     const double t = (double)((K + 64 * s - 1) / (64 * s)) * k_tile +
                      (s > 1 ? 3.0 + 3.5e-6 * (double)(s * M * N) : 0.0);
     if (least == 0.0 || t < least) {
@@ -69,8 +84,8 @@ static int choose_splits(int64_t M, int64_t N, int64_t K) {
 
 // split-K plan of a reduction of length Mr over an N x K weight gradient:
 // sp splits of k_split rows each (a multiple of 64), every split non-empty
-static void split_plan(int64_t N, int64_t K, int64_t Mr, int& sp, int64_t& k_split) {
-  sp = choose_splits(N, K, Mr);
+static void split_plan(int64_t N, int64_t K, int64_t Mr, SplitCost c, int& sp, int64_t& k_split) {
+  sp = choose_splits(N, K, Mr, c);
   k_split = ((Mr + sp - 1) / sp + 63) / 64 * 64;
   sp = (int)((Mr + k_split - 1) / k_split);
 }
@@ -200,7 +215,7 @@ static int linear_bwd(const char* fn, const void* X, const void* W, const void* 
       g.db = (float*)db;
       int sp;
       int64_t ks;
-      split_plan(N, K, M, sp, ks);
+      split_plan(N, K, M, gemm_f32_direct(g, false, false) ? kF32DirectCost : kF32StagedCost, sp, ks);
       if (sp > 1) {
         g.splits = sp;
         g.k_split = ks;
@@ -242,7 +257,7 @@ static int linear_bwd(const char* fn, const void* X, const void* W, const void* 
     g.db = (uint16_t*)db;
     int sp;
     int64_t ks;
-    split_plan(N, K, M, sp, ks);
+    split_plan(N, K, M, kHalfCost, sp, ks);
     if (sp > 1) {
       g.splits = sp;
       g.k_split = ks;

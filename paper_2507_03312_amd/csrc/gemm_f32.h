@@ -37,6 +37,9 @@ struct GemmF32Args {
   float* dbp;
 };
 
+// whether a product takes the direct-to-LDS kernel (with split-K: in splits of
+// multiples of 32)
+bool gemm_f32_direct(const GemmF32Args& g, bool ak, bool bk);
 // db_fused (nullable) tells whether the chosen kernel summed g.db / g.dbp
 hipError_t launch_gemm_f32(GemmF32Args g, bool ak, bool bk, int64_t nbatch, hipStream_t s,
                            bool* db_fused = nullptr);

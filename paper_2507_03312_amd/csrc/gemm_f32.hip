@@ -528,6 +528,11 @@ static bool dma_f32_operand(const float* p, bool kmaj, int64_t ld, int64_t exten
          (kmaj || extent % 4 == 0) && ld * 128 * 4 < ((int64_t)1 << 31);
 }
 
+bool gemm_f32_direct(const GemmF32Args& g, bool ak, bool bk) {
+  return g.K % 32 == 0 && dma_f32_operand(g.A, ak, g.lda, g.M, g.sA0, g.sA1) &&
+         dma_f32_operand(g.B, bk, g.ldb, g.N, g.sB0, g.sB1);
+}
+
 hipError_t launch_gemm_f32(GemmF32Args g, bool ak, bool bk, int64_t nbatch, hipStream_t s, bool* db_fused) {
   const int64_t tiles = ((g.M + kBM - 1) / kBM) * ((g.N + kBN - 1) / kBN);
   const int64_t gy = g.splits > 1 ? g.splits : nbatch;
@@ -535,9 +540,7 @@ hipError_t launch_gemm_f32(GemmF32Args g, bool ak, bool bk, int64_t nbatch, hipS
       (g.splits > 1 && nbatch != 1))
     return hipErrorInvalidValue;
   const dim3 grid((unsigned)tiles, (unsigned)gy);
-  const bool dma = g.K % 32 == 0 && (g.splits == 1 || g.k_split % 32 == 0) &&
-                   dma_f32_operand(g.A, ak, g.lda, g.M, g.sA0, g.sA1) &&
-                   dma_f32_operand(g.B, bk, g.ldb, g.N, g.sB0, g.sB1);
+  const bool dma = gemm_f32_direct(g, ak, bk) && (g.splits == 1 || g.k_split % 32 == 0);
   const bool fuse = dma && !ak && !bk && nbatch == 1 && g.db && (g.splits == 1 || g.dbp);
   if (db_fused) *db_fused = fuse;
   if (dma) {
