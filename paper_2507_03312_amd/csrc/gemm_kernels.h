@@ -1022,12 +1022,13 @@ static bool small_ok(const GemmArgs& g, int64_t nbatch);
 // nk x k_us[o - 1] (nk k tiles of 64) plus o x tile_us for what surrounds the
 // k loops (tile_us[1]: epilogues that read or write a second matrix), and the
 // last round has only as many tiles per CU as are left.  The constants are
-// fitted to 280 measured products with operands from HBM (M 128..25216, N and
-// K 128..3072; forward with bias, GELU or residual, dX, dX through GELU'):
-// the choice is on average 0.5% slower than the fastest, 64 x 128 alone 6%,
-// 128 x 128 alone 10%.  256 x 256 is charged 10% more than its fit: between
-// other products it loses that (the MLP of a 384-wide block, whole: 240 us
-// with it, 234 with 128 x 128, which alone are within 2%).  Examples (us;
+// regression coefficients, set for the choice and not for the times, which
+// they give too small (median 1.1 to 1.4 by tile; a full chip of 128 x 128 tiles does
+// not run at the 1.7 PFLOP/s of 0.62 us): those of least loss on 70% of 2000
+// measured products (M 65..57000, N and K 64..4096, a tenth up to 16384; forward
+// with bias, GELU or residual, dX, dX through GELU'; operands from HBM).  On the
+// other 30% the choice is 0.3% slower than the fastest tile (0.0% past K = 2048), 64 x
+// 128 alone 6%, 128 x 128 alone 13%.  Examples (us;
 // 256 x 256, 128 x 192, 128 x 128, 64 x 128): 12608 x 2304 x 768 dX
 // 49 / 51 / 51 / 58; 12608 x 768 x 3072 forward 78 / 66 / 80 / 87; 16640 x 384
 // x 1536 44 / 34 / 29 / 41; 8320 x 384 x 384 16.6 / 10.0 / 9.0 / 8.9.
@@ -1037,10 +1038,10 @@ struct TileCost {
 };
 static int choose_tiles(const GemmArgs& g, int64_t nbatch) {
   static const TileCost costs[] = {
-      {9, 64, 128, 3, {0.35, 0.56, 0.94}, {0.73, 1.26}},
-      {7, 128, 128, 2, {0.62, 0.60, 0}, {2.37, 2.76}},
-      {5, 128, 192, 2, {0.85, 0.83, 0}, {2.06, 4.35}},
-      {3, 256, 256, 1, {1.20, 0, 0}, {7.2, 13.0}},
+      {9, 64, 128, 3, {0.59, 0.60, 0.79}, {0.93, 1.12}},
+      {7, 128, 128, 2, {0.61, 0.62, 0}, {2.0, 2.7}},
+      {5, 128, 192, 2, {0.78, 0.79, 0}, {2.85, 4.45}},
+      {3, 256, 256, 1, {1.10, 0, 0}, {8.35, 11.55}},
   };
   const int second = g.pre || g.dact || g.resid ? 1 : 0;
   const double nk = (double)(g.K / 64);
