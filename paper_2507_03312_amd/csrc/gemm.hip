@@ -34,17 +34,18 @@ static int64_t most_splits(int64_t M, int64_t N, int64_t K) {
   return std::max<int64_t>(1, std::min<int64_t>({512 / tiles, 16, K / 1024}));
 }
 
-// Cost of a k tile of 64 (us) with one and with two workgroups per CU.
-// Float32: the direct kernel is bound by the matrix cores, so a second workgroup
-// costs nearly a second time; the register-staged one waits for its loads with one
-// workgroup and is slower altogether.  With the half kernel's figures 2276 x 1728
-// over 3174 rows (staged) ran unsplit, 487 us against 319 in 2 splits, and 2298 x
+// Cost of a k tile of 64 (us) with one and with two workgroups per CU, of the
+// direct-to-LDS and the register-staged kernels.  Float32: the direct kernel is
+// bound by the matrix cores, so a second workgroup costs nearly a second time;
+// the register-staged one waits for its loads with one workgroup and is slower
+// altogether.  With the half kernel's figures 2276 x 1728 over 3174 rows
+// (float32, staged) ran unsplit, 487 us against 319 in 2 splits, and 2298 x
 // 220 over 16955 in 7 splits, 382 against 265 in 14.
 struct SplitCost {
   double one, two;
 };
-static constexpr SplitCost kHalfCost = {0.74, 1.07};
-static constexpr SplitCost kF32DirectCost = {4.5, 8.0}, kF32StagedCost = {9.7, 13.5};
+static constexpr SplitCost kHalfCost = {0.9, 1.1}, kHalfStagedCost = {1.6, 1.9};
+static constexpr SplitCost kF32Cost = {4.5, 8.0}, kF32StagedCost = {9.7, 13.5};
 
 // split-K plan for a reduction of length K over an MxN output (the weight
 // gradients, whose outputs have far fewer 128 x 128 tiles than the chip has
@@ -53,16 +54,18 @@ static constexpr SplitCost kF32DirectCost = {4.5, 8.0}, kF32StagedCost = {9.7, 1
 // A k tile of 64 takes c.one with one workgroup per CU and c.two with two
 // (256 + 1 workgroups cost as much as 512; a third round as much again), and
 // each split's float32 partials cost their write and read, 8 bytes per output:
-// 1.8 us per million outputs alone, charged as 3.5 because the partials also
+// 2.3 us per million outputs alone, charged as 3.5 because the partials also
 // push the operands of the neighbouring kernels out of the caches (16640 x 1536
 // x 384 in 14 splits instead of 7: the product and its reduction alone 47.4 ->
 // 43.9 us, the MLP layers around it 2% slower).  Against one workgroup per CU,
 // rounded up, the rule before: 12608 x 2304 x 768 3 -> 4 splits 82 -> 69 us,
 // 12608 x 3072 x 768 2 -> 3 splits 93 -> 78 us with operands from HBM; the
 // ViT-B step, where these run beside the critical path, 10.98 -> 10.55 ms.
-// 90 drawn bf16 gradients (2048 to 40000 rows, 32 to 3072 outputs a side) with
-// every count timed alone: 0.7% slower on average than the fastest count, 0.2%
-// with a charge of 1.8.
+// The half kernels' figures are fitted to 330 gradients with their split counts
+// timed alone (2048 to 65000 rows, 64 to 4096 outputs a side): 0.8% slower on average than
+// the fastest count where the operands are copied directly (0.2% with a charge of 2.3),
+// 0.7% staged.  With 0.74 and 1.07 for both it was 1.8% and 2.8%: 1088 x 3008 over 7168
+// rows unsplit 99 us, in 2 splits 73; 3072 x 1024 over 6076 (staged) 114 and 80.
 static int choose_splits(int64_t M, int64_t N, int64_t K, SplitCost c) {
   const int64_t tiles = ((M + 127) / 128) * ((N + 127) / 128);
   const int64_t most = most_splits(M, N, K);
@@ -215,7 +218,7 @@ static int linear_bwd(const char* fn, const void* X, const void* W, const void* 
       g.db = (float*)db;
       int sp;
       int64_t ks;
-      split_plan(N, K, M, gemm_f32_direct(g, false, false) ? kF32DirectCost : kF32StagedCost, sp, ks);
+      split_plan(N, K, M, gemm_f32_direct(g, false, false) ? kF32Cost : kF32StagedCost, sp, ks);
       if (sp > 1) {
         g.splits = sp;
         g.k_split = ks;
@@ -257,7 +260,7 @@ static int linear_bwd(const char* fn, const void* X, const void* W, const void* 
     g.db = (uint16_t*)db;
     int sp;
     int64_t ks;
-    split_plan(N, K, M, kHalfCost, sp, ks);
+    split_plan(N, K, M, dma_ok(g, operands_aligned(g), false, false) ? kHalfCost : kHalfStagedCost, sp, ks);
     if (sp > 1) {
       g.splits = sp;
       g.k_split = ks;

@@ -876,6 +876,10 @@ static bool aligned_vec(const void* p, int64_t ld, int64_t s0, int64_t s1) {
   return (reinterpret_cast<uintptr_t>(p) & 15u) == 0 && ld % 8 == 0 && s0 % 8 == 0 && s1 % 8 == 0;
 }
 
+static bool operands_aligned(const GemmArgs& g) {
+  return aligned_vec(g.A, g.lda, g.sA0, g.sA1) && aligned_vec(g.B, g.ldb, g.sB0, g.sB1);
+}
+
 // Epilogue mask of a call: 0 with split-K, whose kernels end before it, and
 // EPI_GENERIC for calls that count non-finite outputs (weight gradients).
 static int epilogue_mask(const GemmArgs& g) {
@@ -1152,8 +1156,7 @@ static hipError_t launch_small(const GemmArgs& g, bool ak, bool bk, hipStream_t 
 template <int DT>
 static hipError_t run_gemm(GemmArgs g, bool ak, bool bk, int64_t nbatch, hipStream_t s,
                            bool* db_fused) {
-  const bool vec = aligned_vec(g.A, g.lda, g.sA0, g.sA1) && aligned_vec(g.B, g.ldb, g.sB0, g.sB1);
-  const int cfg = choose_config(g, vec, ak, bk, nbatch);
+  const int cfg = choose_config(g, operands_aligned(g), ak, bk, nbatch);
   const bool fuse = g.db && (cfg == 7 || cfg == 2 || (cfg == 1 && g.splits == 1)) && !ak && !bk &&
                     nbatch == 1 && (g.splits == 1 || g.dbp);
   if (db_fused) *db_fused = fuse;
