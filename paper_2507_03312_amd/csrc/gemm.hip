@@ -1,8 +1,8 @@
 // C ABI of the half GEMMs (linear forward / backward, batched attention
 // products): argument checks, split-K planning and dispatch to the kernels
-// of gemm_kernels.h, which are compiled once per half type in gemm_f16.hip
-// and gemm_bf16.hip; float32 calls (full-precision training) go to the
-// kernels of gemm_f32.hip.
+// of gemm_kernels.h, which are compiled once per half type in three sources
+// each (gemm_f16.hip, gemm_wide_f16.hip, gemm_staged_f16.hip; likewise bf16);
+// float32 calls (full-precision training) go to the kernels of gemm_f32.hip.
 #include <mutex>
 
 #include "gemm_f32.h"

@@ -88,6 +88,9 @@ typedef u32x4 u32x4_any __attribute__((aligned(2)));
 // conditions (rows and vectors outside load the last ones inside): with them forward
 // 1792 x 528 x 192 with residual took 7.4 us, 128 x 904 x 128 with bias 4.7 and 256 x 392
 // x 192 with GELU 6.4; now 6.2, 4.0 and 5.3.
+// In float16 the compiler forms half(x sigma) and half(h gelu') with one
+// instruction that rounds once or through float32, so GELU results of two tile shapes,
+// or of whole and edge tiles, may differ in the last place.
 // pf (nullable): the wave's GELU' or residual operand rows, already loaded
 // in the row layout (16 bytes of row (lane >> 3) + 8 t per entry t).
 // J0: first of the TN accumulator columns handled (of TNA).
@@ -315,9 +318,10 @@ __device__ __forceinline__ void gemm_partials(const GemmArgs& g, const f32x16 (&
 //                     transposes 16-bit elements across groups of 16 lanes, so
 //                     the operand needs no transposition on the way in.
 // Requirements of the copies (checked by the dispatcher; other operands go
-// through StagedOperand): 16-byte aligned operands with leading dimensions and batch strides that are multiples of 8, and every
-// split's k range a multiple of 64.  Rows past M or N read clamped (valid)
-// addresses; their results are never stored.
+// through StagedOperand): 16-byte aligned operands with leading dimensions and
+// batch strides that are multiples of 8, and every split's k range a multiple
+// of 64.  Rows past M or N read clamped (valid) addresses; their results are
+// never stored.
 
 // Position of 16-byte chunk c of row r (k-major: output row of 64 k; mn-major:
 // k row of ROWS outputs) within the row in LDS; its own inverse.  An mn-major
