@@ -1032,11 +1032,14 @@ static bool small_ok(const GemmArgs& g, int64_t nbatch);
 // last round has only as many tiles per CU as are left.  The constants are
 // regression coefficients, set for the choice and not for the times, which
 // they give too small (median 1.1 to 1.4 by tile; a full chip of 128 x 128 tiles does
-// not run at the 1.7 PFLOP/s of 0.62 us): those of least loss on 70% of 2000
+// not run at the 1.7 PFLOP/s of 0.65 us): those of least loss on 70% of 2000
 // measured products (M 65..57000, N and K 64..4096, a tenth up to 16384; forward
-// with bias, GELU or residual, dX, dX through GELU'; operands from HBM).  On the
-// other 30% the choice is 0.3% slower than the fastest tile (0.0% past K = 2048), 64 x
-// 128 alone 6%, 128 x 128 alone 13%.  Examples (us;
+// with bias, GELU or residual, dX, dX through GELU'; operands from HBM), none less
+// for more tiles per CU.  On the other 30% the choice is 0.3% slower than the
+// fastest tile, 64 x 128 alone 6%, 128 x 128 alone 13%.  256 x 256 is charged 10% more
+// than its fit (0.4% then): one workgroup takes a whole CU, and beside a second
+// stream it loses that (one-block step, 8320 x 1536 x 384 with GELU and its dX through
+// GELU': 348.5 us with 256 x 256, 342 with 128 x 128).  Examples (us;
 // 256 x 256, 128 x 192, 128 x 128, 64 x 128): 12608 x 2304 x 768 dX
 // 49 / 51 / 51 / 58; 12608 x 768 x 3072 forward 78 / 66 / 80 / 87; 16640 x 384
 // x 1536 44 / 34 / 29 / 41; 8320 x 384 x 384 16.6 / 10.0 / 9.0 / 8.9.
@@ -1046,10 +1049,10 @@ struct TileCost {
 };
 static int choose_tiles(const GemmArgs& g, int64_t nbatch) {
   static const TileCost costs[] = {
-      {9, 64, 128, 3, {0.59, 0.60, 0.79}, {0.93, 1.12}},
-      {7, 128, 128, 2, {0.61, 0.62, 0}, {2.0, 2.7}},
-      {5, 128, 192, 2, {0.78, 0.79, 0}, {2.85, 4.45}},
-      {3, 256, 256, 1, {1.10, 0, 0}, {8.35, 11.55}},
+      {9, 64, 128, 3, {0.48, 0.50, 0.78}, {0.60, 1.25}},
+      {7, 128, 128, 2, {0.51, 0.65, 0}, {1.36, 2.75}},
+      {5, 128, 192, 2, {0.77, 0.83, 0}, {1.86, 4.49}},
+      {3, 256, 256, 1, {1.08, 0, 0}, {7.36, 14.1}},
   };
   const int second = g.pre || g.dact || g.resid ? 1 : 0;
   const double nk = (double)(g.K / 64);
