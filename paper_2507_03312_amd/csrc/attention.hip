@@ -903,13 +903,14 @@ template <int DT>
 hipError_t launch_bwd(const uint16_t* qkv, const uint16_t* P, const uint16_t* dO, uint16_t* dqkv, int B,
                       int T, int H, int ldP, float scale, hipStream_t s) {
   const dim3 grid((unsigned)(B * H));
-// P and dS in K's place where that lets a CU hold more workgroups and the grid
-// has them (us, shared / separate: 256 workgroups of 32 tokens 5.2 / 4.9, of 64
-// tokens 7.2 / 6.7, of 96, where two fit either way, 10.5 / 10.0; 1536 workgroups
-// of 65 tokens 25.3 / 29.1, that with 96 rows kept)
+// P and dS in K's place where that lets a CU hold three workgroups instead of two
+// (80 rows) and the grid has them (us, shared / separate: 516 workgroups of 65
+// tokens 15.1 / 16.0, of 80 tokens 17.0 / 18.7; from 1026 on equal).  With more
+// workgroups per CU either way it loses: 1536 of 64 tokens 30.8 / 26.7, 3072 of 32
+// tokens 29.5 / 27.4, and on small grids 256 of 32 tokens 5.2 / 4.9
 #define MPX_B(Rv)                                                                                            \
-  if constexpr (bwd_per_cu(Rv, true) > bwd_per_cu(Rv, false)) {                                              \
-    if (B * (int64_t)H > 256 * bwd_per_cu(Rv, false)) {                                                      \
+  if constexpr (bwd_per_cu(Rv, false) == 2 && bwd_per_cu(Rv, true) > 2) {                                    \
+    if (B * (int64_t)H > 512) {                                                                              \
       attn_bwd_kernel<DT, Rv, true><<<grid, (Rv + 31) / 32 * 64, 0, s>>>(qkv, P, dO, dqkv, T, H, ldP, scale); \
       break;                                                                                                 \
     }                                                                                                        \
