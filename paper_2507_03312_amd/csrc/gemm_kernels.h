@@ -207,8 +207,9 @@ __device__ __forceinline__ void gemm_epilogue_lds(const GemmArgs& g, const f32x1
   };
   int bad = 0;
   // edge tiles: GELU of every step ahead of the conditions around the stores, which
-  // keep the steps apart.  half(x sigma) one value at a time, as behind them
-  constexpr bool kAhead = EDGE && E != EPI_GENERIC && (E & EPI_GELU) != 0;
+  // keep the steps apart.  half(x sigma) one value at a time, as behind them.  Not
+  // the 16 steps of 256 x 256 tiles, which spill
+  constexpr bool kAhead = EDGE && E != EPI_GENERIC && (E & EPI_GELU) != 0 && TM <= 2;
   u32x4 gel[kAhead ? STEPS : 1];
   if constexpr (kAhead) {
 #pragma unroll
