@@ -59,30 +59,30 @@ DEFAULT_CONFIG = "vit_b"
 # they no longer match, the figure is stale and reported as null.
 TRAFFIC = {
     "vit_block/blk0.up.fwd": {
-        "fetch_kib": 13913.4, "write_kib": 49920.0,
-        "fetch_factor": 262144.0 / 131086.0, "write_factor": 262144.0 / 262144.0,
+        "fetch_kib": 13915.3, "write_kib": 49920.0,
+        "fetch_factor": 262144.0 / 131086.1, "write_factor": 262144.0 / 262144.0,
         "sources": {
-            "paper_2507_03312_amd/csrc/gemm_kernels.h": "9a0421355c918120cad690809a787fac6d19db8f2a81df019c80704d996b6448",
+            "paper_2507_03312_amd/csrc/gemm_kernels.h": "e40a4035e710177296d77fb61c64bcd13ab8ff398d4aac717f99bfad1161b4e8",
             "paper_2507_03312_amd/csrc/dma.h": "61ef692c90dd4fb350d22bc5a438fad642f5f8242b05362dc6c741854adf5ace",
             "paper_2507_03312_amd/csrc/mfma.h": "46e04f5162db64f2c8dc7bd5c5aae35c9ba491888000bfd3597337920e363231",
             "paper_2507_03312_amd/csrc/common.h": "2084a1c1294723c666ae58a2f812b765b2e5ea388fca5027c911b15626f0d620",
         },
     },
     "vit_s/blk0.up.fwd": {
-        "fetch_kib": 25185.4, "write_kib": 99840.0,
-        "fetch_factor": 262144.0 / 131085.9, "write_factor": 262144.0 / 262144.0,
+        "fetch_kib": 25216.7, "write_kib": 99840.0,
+        "fetch_factor": 262144.0 / 131086.0, "write_factor": 262144.0 / 262144.0,
         "sources": {
-            "paper_2507_03312_amd/csrc/gemm_kernels.h": "9a0421355c918120cad690809a787fac6d19db8f2a81df019c80704d996b6448",
+            "paper_2507_03312_amd/csrc/gemm_kernels.h": "e40a4035e710177296d77fb61c64bcd13ab8ff398d4aac717f99bfad1161b4e8",
             "paper_2507_03312_amd/csrc/dma.h": "61ef692c90dd4fb350d22bc5a438fad642f5f8242b05362dc6c741854adf5ace",
             "paper_2507_03312_amd/csrc/mfma.h": "46e04f5162db64f2c8dc7bd5c5aae35c9ba491888000bfd3597337920e363231",
             "paper_2507_03312_amd/csrc/common.h": "2084a1c1294723c666ae58a2f812b765b2e5ea388fca5027c911b15626f0d620",
         },
     },
     "vit_b/blk0.up.fwd": {
-        "fetch_kib": 70043.8, "write_kib": 151296.0,
+        "fetch_kib": 69938.8, "write_kib": 151296.0,
         "fetch_factor": 262144.0 / 131086.0, "write_factor": 262144.0 / 262144.0,
         "sources": {
-            "paper_2507_03312_amd/csrc/gemm_kernels.h": "9a0421355c918120cad690809a787fac6d19db8f2a81df019c80704d996b6448",
+            "paper_2507_03312_amd/csrc/gemm_kernels.h": "e40a4035e710177296d77fb61c64bcd13ab8ff398d4aac717f99bfad1161b4e8",
             "paper_2507_03312_amd/csrc/dma.h": "61ef692c90dd4fb350d22bc5a438fad642f5f8242b05362dc6c741854adf5ace",
             "paper_2507_03312_amd/csrc/mfma.h": "46e04f5162db64f2c8dc7bd5c5aae35c9ba491888000bfd3597337920e363231",
             "paper_2507_03312_amd/csrc/common.h": "2084a1c1294723c666ae58a2f812b765b2e5ea388fca5027c911b15626f0d620",
